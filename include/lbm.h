@@ -60,7 +60,9 @@ typedef enum { LBM_FP64 = 0, LBM_FP32_SHIFTED = 1 } lbm_prec;
  * workgroup advances a tile 58 columns wide by two time steps per launch and
  * keeps the intermediate populations in LDS (temporal blocking; a reducing
  * step ends a launch, and checkpoint boundaries and odd counts run single
- * steps on BLOCK).  The tile: FP64, 8 wavefronts of two rows each, 10 rows;
+ * steps on BLOCK).  AUTO runs periodic lattices of at most 16 rows or 1024
+ * nodes (recording and checkpointing off, tile_rows = 0) up to 16 steps per
+ * launch, or any number, with the populations in LDS.  The tile: FP64, 8 wavefronts of two rows each, 10 rows;
  * FP32, 16 wavefronts of one row, 10 rows, or on lattices of at least 4096
  * such tiles 12 wavefronts of two rows, 18 rows.  AUTO is BLOCK2.
  * AA: one population buffer updated in place with the AA access pattern
@@ -326,12 +328,14 @@ int lbm_init_batched(lbm_batch** ctx, int B, const lbm_params* p, void* f_a, voi
                      const double* rho0, const double* ux0, const double* uy0, void* stream);
 /* nsteps time steps of every lattice (asynchronous).  Persistent mode: one
  * launch in which one workgroup per lattice loops over the steps.  Grouped
- * mode: launches over all lattices at once, two steps per launch (whole
- * columns per workgroup when every lattice is periodic and at most 16 rows
- * tall, else the two-step tiles), an odd last step on its own, replayed as
- * HIP graphs of 128 steps.  Launches replayed from a graph keep the step
- * numbers of their capture, so the step that lbm_status_batched names is
- * exact only within the first capture. */
+ * mode: launches over all lattices at once, two steps per launch (two-step
+ * tiles), an odd last step on its own, replayed as HIP graphs of 128 steps.
+ * Launches replayed from a graph keep the step numbers of their capture, so
+ * the step that lbm_status_batched names is exact only within the first
+ * capture.  When every lattice is periodic and at most 16 rows tall, or has at
+ * most 1024 nodes, both modes run up to 16 steps per launch (any number when
+ * every lattice has at most 1024 nodes) on workgroups that keep all rows of
+ * some columns in LDS (persistent mode: only in the latter case). */
 int lbm_step_batched(lbm_batch* ctx, int64_t nsteps, void* stream);
 /* Choose how lbm_step_batched runs: LBM_BATCH_AUTO (default: grouped when some
  * lattice has more than 32 strip-rows, i.e. more than two per wavefront of

@@ -1,14 +1,15 @@
-// liblbm.so: many independent lattices advanced together, in one of two ways.
+// liblbm.so: many independent lattices advanced together, in one of three ways.
 //
 // Persistent: each lattice (its own size, EOS, relaxation times and FP32
 // shift) is owned by one workgroup of 16 wavefronts that loops over the time
 // steps with a workgroup barrier between steps: neighbouring nodes of a
 // lattice are only ever touched by that workgroup, so no grid-wide
 // synchronisation is needed.  Best for many small lattices (no launch per step).
-// Grouped: one launch per time step over all lattices, one wavefront per
-// (lattice, 62-column strip, row); the launches of a chunk of steps are
-// replayed as a HIP graph.  Best when a large lattice would keep one
-// workgroup busy for many items per step while most CUs idle.
+// Grouped: two steps per launch over the tiles of all lattices; the launches of a
+// chunk of steps are replayed as a HIP graph.  Best when a large lattice would keep
+// one workgroup busy for many items per step while most CUs idle.
+// Batches of short or small periodic lattices run neither but the strip kernel of
+// lbm_strip.h: many steps per launch with the populations in LDS.
 // Populations of all lattices are packed back to back in one pair of buffers;
 // scalar fields are packed in the same lattice order ([ny_b][nx_b] each).
 // The per-node arithmetic is the fused step of lbm_device.h: pull with
@@ -19,11 +20,13 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "lbm.h"
 #include "lbm_device.h"
 #include "lbm_internal.h"
+#include "lbm_strip.h"
 
 namespace {
 
@@ -35,6 +38,7 @@ struct BatchItem {
     StepArgs A;           // per-lattice arguments (src/dst filled in the kernel)
     size_t off_bytes;     // byte offset of the lattice in each population buffer
     long long cell_off;   // offset of the lattice in the packed scalar fields
+    int cols, out;        // columns a strip workgroup holds and advances (lbm_strip.h)
 };
 
 template <typename T, int MODE>
@@ -162,146 +166,33 @@ void k_batch_step2(const BatchItem* items, const int* tile_off, int B, char* buf
     step2_tile<T, MODE_STEP, WALLS>(A, tile % strips, tile / strips, S);
 }
 
-// Two steps of short periodic lattices (ny <= kFullRows, periodic in y): a workgroup of
-// 64 * max(ny) threads owns a 58-column strip over ALL rows of its lattice, wave k row k.
-// The rows wrap inside the workgroup, so unlike step2_tile there is no ring of rows; only
-// the three-column ring in x is recomputed.  Same phases and node arithmetic as step2_tile.
-constexpr int kFullRows = 16;
-
-// The lattice's EOS record in LDS (read by node_psi), except for 16-row FP64 workgroups:
-// their 80 KB of LDS leave no room for it beside a second workgroup per CU.
-template <bool IN_LDS>
-struct FullEos {
-    DevEos eos;
-    __device__ const DevEos& get(const StepArgs&) const { return eos; }
-    __device__ void put(const StepArgs& A) { eos = A.eos; }
-};
-template <>
-struct FullEos<false> {
-    __device__ const DevEos& get(const StepArgs& A) const { return A.eos; }
-    __device__ void put(const StepArgs&) {}
-};
-
-// LDS sized for ROWS rows (4, 8 or kFullRows, the smallest that holds max(ny)): shorter
-// lattices fit more workgroups per CU (a 16-row FP32 workgroup takes 45 KB whatever its
-// height, i.e. three per CU)
-template <typename T, int ROWS>
-struct FullLds : FullEos<sizeof(T) == 4 || ROWS < kFullRows> {
-    T sps[ROWS][64];
-    T smv[8][ROWS][64];
-    double sg0[ROWS][64];
-};
-
-template <typename T, int ROWS, bool NT>
-__global__ __launch_bounds__(64 * ROWS) void k_batch_full2(const BatchItem* items, const int* tile_off, int B,
-                                                            char* buf0, char* buf1, int cur, long long step)
+// Many steps of short or small periodic lattices (strip_steps): workgroup w takes strip w of
+// the table (lattice, first column).
+template <typename T, int CAP>
+__global__ __launch_bounds__(CAP)
+void k_batch_strip(const BatchItem* items, const int2* strips, char* buf0, char* buf1, int cur, int halo, int nsteps,
+                   int step)
 {
-    __shared__ FullLds<T, ROWS> S;
-    const int w = blockIdx.x;
-    if (w >= tile_off[B]) return;
-    int lo = 0, hi = B;  // tile_off[lo] <= w < tile_off[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (tile_off[mid] <= w) lo = mid;
-        else hi = mid;
-    }
-    StepArgs A = items[lo].A;
-    const size_t off = items[lo].off_bytes;
-    A.src = (cur ? buf1 : buf0) + off;
-    A.dst = (cur ? buf0 : buf1) + off;
-    A.step = step;
-    const int strip = w - tile_off[lo];
-    const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const bool row = k < A.ny;  // waves beyond this lattice's rows only keep the barriers
-    const int km = k == 0 ? A.ny - 1 : k - 1, kp = k + 1 == A.ny ? 0 : k + 1;
-    const int x0 = strip * k2Cols, W = min(k2Cols, A.nx - x0);
-    const int dl = l < 3 ? 3 - l : (l > W + 2 ? l - (W + 2) : 0);
-    Lane L;
-    L.lane = l;
-    L.valid = dl <= 3;
-    L.interior = dl == 0;
-    // columns of lanes with dl <= 3 lie in [-3, nx + 2]: one wrap each way unless nx < 3
-    int x = x0 - 3 + l;
-    if (A.nx >= 3) x = x < 0 ? x + A.nx : (x >= A.nx ? x - A.nx : x);
-    else x = (x % A.nx + A.nx) % A.nx;
-    if (dl > 3) x = 0;
-    L.x = x;
-    L.xm = x == 0 ? A.nx - 1 : x - 1;
-    L.xp = x == A.nx - 1 ? 0 : x + 1;
-    Acc acc = {0.0, 0.0, 0.0};
-    // 1. step t: pull, rho, psi (the EOS record goes to LDS while the pull is in flight,
-    //    as in step2_tile)
-    if (threadIdx.x == 0) S.put(A);
-    Row<T> R;
-    double dr = 0.0;
-    T ps = (T)0;
-    if (row && dl <= 3) {
-        const View<T> V = make_view<T>(A.src, A.plane);
-        pull<T>(V, A, L.x, L.xm, L.xp, k, R.g0, R.g);
-    }
-    __syncthreads();
-    if (row && dl <= 3) {
-        dr = node_drho<T>(R.g0, R.g);
-        ps = node_psi<T>(A, S.get(A), dr, true);
-    }
-    S.sps[k][l] = ps;
-    __syncthreads();
-    // 2. step t: collide the strip grown by 2 columns into LDS
-    if (row && dl <= 2) {
-        T Ftx, Fty;
-        force_tilde<T>(A, S.sps[km][l - 1], S.sps[km][l], S.sps[km][l + 1], S.sps[k][l - 1], S.sps[k][l + 1],
-                       S.sps[kp][l - 1], S.sps[kp][l], S.sps[kp][l + 1], Ftx, Fty);
-        T o[9];
-        double o0;
-        node_collide<T, MODE_STEP>(A, L, k, R, dr, ps, Ftx, Fty, acc, o, o0);
-#pragma unroll
-        for (int i = 1; i < 9; ++i) S.smv[i - 1][k][l] = o[i];
-        S.sg0[k][l] = o0;
-    }
-    __syncthreads();
-    // 3. step t+1: pull from LDS (rows wrap), psi(t+1)
-    if (row && dl <= 1) {
-        R.g0 = S.sg0[k][l];
-        R.g[1] = S.smv[0][k][l - 1];
-        R.g[3] = S.smv[2][k][l + 1];
-        R.g[2] = S.smv[1][km][l];
-        R.g[5] = S.smv[4][km][l - 1];
-        R.g[6] = S.smv[5][km][l + 1];
-        R.g[4] = S.smv[3][kp][l];
-        R.g[7] = S.smv[6][kp][l + 1];
-        R.g[8] = S.smv[7][kp][l - 1];
-        dr = node_drho<T>(R.g0, R.g);
-        ps = node_psi<T>(A, S.get(A), dr, true, 1);
-        S.sps[k][l] = ps;
-    }
-    __syncthreads();
-    // 4. step t+1: collide the strip and store
-    if (row && dl == 0) {
-        T Ftx, Fty;
-        force_tilde<T>(A, S.sps[km][l - 1], S.sps[km][l], S.sps[km][l + 1], S.sps[k][l - 1], S.sps[k][l + 1],
-                       S.sps[kp][l - 1], S.sps[kp][l], S.sps[kp][l + 1], Ftx, Fty);
-        update_node<T, MODE_STEP, NT>(A, L, k, R, dr, ps, Ftx, Fty, acc);
-    }
+    __shared__ StripLds<T, CAP> S;
+    const int b = __builtin_amdgcn_readfirstlane(strips[blockIdx.x].x);
+    const int x0 = __builtin_amdgcn_readfirstlane(strips[blockIdx.x].y);
+    const StepArgs A = items[b].A;
+    const size_t off = items[b].off_bytes;
+    strip_steps<T, CAP, false>(A, (cur ? buf1 : buf0) + off, (cur ? buf0 : buf1) + off, x0, items[b].cols, items[b].out,
+                               halo, nsteps, step, nullptr, S);
 }
 
-template <typename T, bool NT>
-void launch_full2_t(int max_ny, dim3 g, dim3 b, hipStream_t s, const BatchItem* it, const int* off, int B, char* b0,
-                    char* b1, int cur, long long st)
+template <typename T>
+void launch_batch_strip(int threads, dim3 g, hipStream_t s, const BatchItem* it, const int2* strips, char* b0, char* b1,
+                        int cur, int halo, int nsteps, int step)
 {
-    if (max_ny <= 4) hipLaunchKernelGGL((k_batch_full2<T, 4, NT>), g, b, 0, s, it, off, B, b0, b1, cur, st);
-    else if (max_ny <= 8) hipLaunchKernelGGL((k_batch_full2<T, 8, NT>), g, b, 0, s, it, off, B, b0, b1, cur, st);
-    else hipLaunchKernelGGL((k_batch_full2<T, kFullRows, NT>), g, b, 0, s, it, off, B, b0, b1, cur, st);
-}
-
-// nt: streaming stores, when both population buffers of the batch are small (kStreamBytes)
-// (as for a single lattice)
-void launch_full2(bool f32, bool nt, int max_ny, dim3 g, dim3 b, hipStream_t s, const BatchItem* it, const int* off,
-                  int B, char* b0, char* b1, int cur, long long st)
-{
-    if (f32 && nt) launch_full2_t<float, true>(max_ny, g, b, s, it, off, B, b0, b1, cur, st);
-    else if (f32) launch_full2_t<float, false>(max_ny, g, b, s, it, off, B, b0, b1, cur, st);
-    else if (nt) launch_full2_t<double, true>(max_ny, g, b, s, it, off, B, b0, b1, cur, st);
-    else launch_full2_t<double, false>(max_ny, g, b, s, it, off, B, b0, b1, cur, st);
+    auto go = [&](auto cap) {
+        constexpr int CAP = decltype(cap)::value;
+        hipLaunchKernelGGL((k_batch_strip<T, CAP>), g, dim3(threads), 0, s, it, strips, b0, b1, cur, halo, nsteps, step);
+    };
+    if (threads <= 256) go(std::integral_constant<int, 256>());
+    else if (threads <= 512) go(std::integral_constant<int, 512>());
+    else go(std::integral_constant<int, 1024>());
 }
 
 template <typename T>
@@ -351,9 +242,10 @@ struct Layout {
     std::vector<int> ld;
     std::vector<int> item_off;      // [B+1] one-step grouped items (strips x rows) before each lattice
     std::vector<int> tile_off;      // [B+1] two-step grouped tiles before each lattice
-    std::vector<int> strip_off;     // [B+1] two-step full-height strips before each lattice
-    int any_walls, max_ny;
-    size_t off_items, off_item_off, off_tile_off, off_strip_off, ws_bytes;
+    StripPlan strip;                // how the strip kernel runs these lattices (0 threads: it does not)
+    std::vector<int2> strips;       // its workgroups: lattice, first column
+    int any_walls;
+    size_t off_items, off_item_off, off_tile_off, off_strips, ws_bytes;
 };
 
 int batch_layout(int B, const lbm_params* p, Layout& L)
@@ -367,9 +259,7 @@ int batch_layout(int B, const lbm_params* p, Layout& L)
     L.ld.assign(B, 0);
     L.item_off.assign(B + 1, 0);
     L.tile_off.assign(B + 1, 0);
-    L.strip_off.assign(B + 1, 0);
     L.any_walls = 0;
-    L.max_ny = 0;
     for (int b = 0; b < B; ++b) {
         if (p[b].prec != p[0].prec) {
             lbm_set_error("lbm batched: every lattice must use the same storage precision");
@@ -396,17 +286,20 @@ int batch_layout(int B, const lbm_params* p, Layout& L)
         L.item_off[b + 1] = L.item_off[b] + (int)items;
         const int rows2 = k2waves_of_prec(p[0].prec) - 6;
         L.tile_off[b + 1] = L.tile_off[b] + ((p[b].nx + k2Cols - 1) / k2Cols) * ((p[b].ny + rows2 - 1) / rows2);
-        L.strip_off[b + 1] = L.strip_off[b] + (p[b].nx + k2Cols - 1) / k2Cols;
         L.any_walls |= p[b].walls != 0;
-        L.max_ny = p[b].ny > L.max_ny ? p[b].ny : L.max_ny;
     }
+    L.strip = strip_plan(B, p);
+    if (L.strip.threads)
+        for (int b = 0; b < B; ++b)
+            for (int x = 0, out = strip_out(p[b], L.strip.threads, L.strip.steps); x < p[b].nx; x += out)
+                L.strips.push_back(int2{b, x});
     // workspace: per-lattice error words, the item records, the grouped-step item offsets
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
     L.off_items = al((size_t)B * 2 * sizeof(unsigned));
     L.off_item_off = L.off_items + al((size_t)B * sizeof(BatchItem));
     L.off_tile_off = L.off_item_off + al((size_t)(B + 1) * sizeof(int));
-    L.off_strip_off = L.off_tile_off + al((size_t)(B + 1) * sizeof(int));
-    L.ws_bytes = L.off_strip_off + al((size_t)(B + 1) * sizeof(int));
+    L.off_strips = L.off_tile_off + al((size_t)(B + 1) * sizeof(int));
+    L.ws_bytes = L.off_strips + al(L.strips.size() * sizeof(int2));
     return LBM_OK;
 }
 
@@ -423,9 +316,9 @@ struct lbm_batch {
     BatchItem* items;
     int* item_off;          // device copies of Layout::item_off and Layout::tile_off
     int* tile_off;
-    int* strip_off;         // device copy of Layout::strip_off (full-height strips)
-    int full;               // 1: every lattice is periodic with ny <= kFullRows (full-height two-step)
-    int grouped;            // 1: one grouped launch per step; 0: persistent workgroups
+    int2* strips;           // device copy of Layout::strips
+    int strip;              // 1: the strip kernel runs every step
+    int grouped;            // else 1: two-step grouped launches; 0: persistent workgroups
     hipStream_t cap;        // capture stream (default priority)
     hipGraphExec_t exec[2]; // per starting buffer: the persistent launch of `graph_steps` steps, or
                             // kGroupChunk two-step grouped launches
@@ -434,6 +327,15 @@ struct lbm_batch {
 
 namespace {
 constexpr int kGroupChunk = 64;  // two-step grouped launches per replayed graph (128 steps)
+
+// Which kernel a mode runs.  The strip kernel wherever its plan holds: it is the grouped mode of
+// short lattices (measured on MI355X, 64 planar lattices of 4 rows, FP32: 2.8 against 4.3
+// us/step with two steps per launch), and the persistent one when every lattice is resident
+// (333 lattices of 200 x 2, FP64: 2.3 against 11.6 us/step with the populations in HBM).
+int strip_mode(const Layout& L, int mode)
+{
+    return L.strip.threads && (mode != LBM_BATCH_PERSISTENT || L.strip.steps == kResidentSteps);
+}
 
 // persistent unless some lattice gives one workgroup more than two items per wave and step
 int auto_grouped(const Layout& L, int B)
@@ -481,8 +383,8 @@ int lbm_init_batched(lbm_batch** out, int B, const lbm_params* p, void* f_a, voi
     c->items = (BatchItem*)((char*)ws + L.off_items);
     c->item_off = (int*)((char*)ws + L.off_item_off);
     c->tile_off = (int*)((char*)ws + L.off_tile_off);
-    c->strip_off = (int*)((char*)ws + L.off_strip_off);
-    c->full = !L.any_walls && L.max_ny <= kFullRows;
+    c->strips = (int2*)((char*)ws + L.off_strips);
+    c->strip = strip_mode(L, LBM_BATCH_AUTO);
     c->grouped = auto_grouped(L, B);
     std::vector<BatchItem> host(B);
     std::vector<unsigned> err0(2 * (size_t)B);
@@ -520,6 +422,8 @@ int lbm_init_batched(lbm_batch** out, int B, const lbm_params* p, void* f_a, voi
         A.err = c->err + 2 * b;
         host[b].off_bytes = L.off[b];
         host[b].cell_off = L.cells[b];
+        host[b].cols = L.strip.threads ? strip_cols(P, L.strip.threads) : 0;
+        host[b].out = L.strip.threads ? strip_out(P, L.strip.threads, L.strip.steps) : 0;
         err0[2 * b] = 0u;
         err0[2 * b + 1] = 0xffffffffu;
     }
@@ -529,8 +433,9 @@ int lbm_init_batched(lbm_batch** out, int B, const lbm_params* p, void* f_a, voi
                 "batch item offsets") ||
         !hip_ok(hipMemcpyAsync(c->tile_off, L.tile_off.data(), sizeof(int) * (B + 1), hipMemcpyHostToDevice, s),
                 "batch tile offsets") ||
-        !hip_ok(hipMemcpyAsync(c->strip_off, L.strip_off.data(), sizeof(int) * (B + 1), hipMemcpyHostToDevice, s),
-                "batch strip offsets") ||
+        (!L.strips.empty() && !hip_ok(hipMemcpyAsync(c->strips, L.strips.data(), sizeof(int2) * L.strips.size(),
+                                                     hipMemcpyHostToDevice, s),
+                                      "batch strips")) ||
         !hip_ok(hipMemcpyAsync(c->err, err0.data(), sizeof(unsigned) * 2 * B, hipMemcpyHostToDevice, s), "batch errors") ||
         !hip_ok(hipStreamSynchronize(s), "batch init sync")) {
         delete c;
@@ -559,13 +464,9 @@ static bool launch_grouped(lbm_batch* c, int n, int cur, int64_t step0, hipStrea
     const bool f32 = c->prec == LBM_FP32_SHIFTED, w = c->L.any_walls != 0;
     const dim3 g2(c->L.tile_off[c->B]), b2(64 * k2waves_of_prec(c->prec));
     int k = 0;
-    const dim3 gf(c->L.strip_off[c->B]), bf(64 * c->L.max_ny);
     for (; k + 1 < n; k += 2) {
         const long long st = (long long)(step0 + k);
-        if (c->full)
-            launch_full2(f32, 2 * c->L.off[c->B] <= kStreamBytes, c->L.max_ny, gf, bf, s, it, c->strip_off, c->B,
-                         c->buf[0], c->buf[1], cur, st);
-        else if (f32 && !w) hipLaunchKernelGGL((k_batch_step2<float, false>), g2, b2, 0, s, it, c->tile_off, c->B, c->buf[0], c->buf[1], cur, st);
+        if (f32 && !w) hipLaunchKernelGGL((k_batch_step2<float, false>), g2, b2, 0, s, it, c->tile_off, c->B, c->buf[0], c->buf[1], cur, st);
         else if (f32) hipLaunchKernelGGL((k_batch_step2<float, true>), g2, b2, 0, s, it, c->tile_off, c->B, c->buf[0], c->buf[1], cur, st);
         else if (!w) hipLaunchKernelGGL((k_batch_step2<double, false>), g2, b2, 0, s, it, c->tile_off, c->B, c->buf[0], c->buf[1], cur, st);
         else hipLaunchKernelGGL((k_batch_step2<double, true>), g2, b2, 0, s, it, c->tile_off, c->B, c->buf[0], c->buf[1], cur, st);
@@ -600,7 +501,8 @@ int lbm_set_batch_mode(lbm_batch* c, int mode)
 {
     if (!c || mode < LBM_BATCH_AUTO || mode > LBM_BATCH_GROUPED) return LBM_EINVAL;
     const int g = mode == LBM_BATCH_AUTO ? auto_grouped(c->L, c->B) : (mode == LBM_BATCH_GROUPED);
-    if (g != c->grouped) {
+    const int strip = strip_mode(c->L, mode);
+    if (g != c->grouped || strip != c->strip) {
         for (int k = 0; k < 2; ++k)
             if (c->exec[k]) {
                 (void)hipGraphExecDestroy(c->exec[k]);
@@ -608,6 +510,7 @@ int lbm_set_batch_mode(lbm_batch* c, int mode)
             }
         c->graph_steps = 0;
         c->grouped = g;
+        c->strip = strip;
     }
     return LBM_OK;
 }
@@ -646,11 +549,34 @@ static int step_grouped(lbm_batch* c, int64_t nsteps, hipStream_t s)
     return LBM_OK;
 }
 
+// strip kernel: launches of up to L.strip.steps steps, as equal as they come
+static int step_strips(lbm_batch* c, int64_t nsteps, hipStream_t s)
+{
+    const int halo = strip_halo(c->L.strip.steps);
+    while (nsteps > 0) {
+        const int64_t launches = (nsteps + c->L.strip.steps - 1) / c->L.strip.steps;
+        const int n = (int)((nsteps + launches - 1) / launches);
+        const dim3 g((unsigned)c->L.strips.size());
+        if (c->prec == LBM_FP32_SHIFTED)
+            launch_batch_strip<float>(c->L.strip.threads, g, s, c->items, c->strips, c->buf[0], c->buf[1], c->cur, halo, n,
+                                      (int)c->step);
+        else
+            launch_batch_strip<double>(c->L.strip.threads, g, s, c->items, c->strips, c->buf[0], c->buf[1], c->cur, halo, n,
+                                       (int)c->step);
+        if (!hip_ok(hipGetLastError(), "k_batch_strip launch")) return LBM_EHIP;
+        c->cur ^= 1;
+        c->step += n;
+        nsteps -= n;
+    }
+    return LBM_OK;
+}
+
 int lbm_step_batched(lbm_batch* c, int64_t nsteps, void* stream)
 {
     if (!c || nsteps < 0) return LBM_EINVAL;
     if (nsteps == 0) return LBM_OK;
     hipStream_t s = (hipStream_t)stream;
+    if (c->strip) return step_strips(c, nsteps, s);
     if (c->grouped) return step_grouped(c, nsteps, s);
     // the persistent launch is captured once per (step count, starting buffer) and replayed
     if (c->graph_steps != nsteps) {

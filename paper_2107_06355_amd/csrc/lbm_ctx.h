@@ -2,6 +2,7 @@
 #pragma once
 
 #include "lbm_device.h"
+#include "lbm_strip.h"
 
 struct lbm_ctx {
     lbm_params P;
@@ -23,6 +24,8 @@ struct lbm_ctx {
     int blk2, grid2;  // LBM_VARIANT_BLOCK2: two-step launches and their grid
     bool rows2;       // two-step tiles with two rows per wave (k_step2_rows2)
     lbmk::TwoStepShape shape;  // the two-step tile it runs (lbm_params.tile_rows; timed for -1)
+    // short and small periodic lattices: many steps per launch (lbm_strip.h; 0 threads: not)
+    lbmk::StripPlan strip;
     // checkpoints for the adjoint: the state f*(t) at every t = K*slot
     void* ckpt;
     int64_t ckpt_slots;

@@ -31,6 +31,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 
 #include "lbm.h"
 #include "lbm_ctx.h"
@@ -238,6 +239,17 @@ void k_step2_rows2(StepArgs A)
     int strip, band;
     if (!two_step_tile(A, logical, strip, band)) return;  // whole workgroup leaves together
     step2_tile_rows<T, MODE, WALLS, NT, k2rWavesOf<T>, 2>(A, strip, band, S);
+}
+
+// Short and small periodic lattices: nsteps steps per launch (strip_steps; the shape strip_plan
+// picks).  One partial per workgroup when REDUCE.
+template <typename T, int CAP, bool REDUCE>
+__global__ __launch_bounds__(CAP)
+void k_strip(StepArgs A, int cols, int out, int halo, int nsteps)
+{
+    __shared__ StripLds<T, CAP> S;
+    strip_steps<T, CAP, REDUCE>(A, A.src, A.dst, (int)blockIdx.x * out, cols, out, halo, nsteps, 0,
+                                A.partials + 3 * (size_t)blockIdx.x, S);
 }
 
 // Fixed-order FP64 reduction of the per-wave partials, two passes: block b sums
@@ -590,6 +602,13 @@ bool launch_record_step(lbm_ctx* c, void* rec, hipStream_t s)
     return hip_ok(hipGetLastError(), "k_step_blk(record) launch");
 }
 
+// workgroups of a strip launch (and partials of a reducing one)
+int strip_groups(const lbm_ctx* c)
+{
+    const int out = strip_out(c->P, c->strip.threads, c->strip.steps);
+    return (c->P.nx + out - 1) / out;
+}
+
 // two steps in one launch (LBM_VARIANT_BLOCK2): source buf[cur], result in buf[cur ^ 1];
 // rec non-NULL: also record both steps (rec, then rec + one step's record)
 template <typename T>
@@ -638,6 +657,28 @@ bool launch_step2(lbm_ctx* c, void* rec, hipStream_t s, bool reduce = false)
         else hipLaunchKernelGGL((k_step2_blk<T, MODE_STEP, false>), g, b, 0, s, A);
     }
     return hip_ok(hipGetLastError(), "k_step2_blk launch");
+}
+
+// n steps in one launch of the strip kernel: source buf[cur], result in buf[cur ^ 1]
+template <typename T>
+bool launch_strip(lbm_ctx* c, int n, bool reduce, hipStream_t s)
+{
+    StepArgs A = c->args;
+    A.src = c->buf[c->cur];
+    A.dst = c->buf[c->cur ^ 1];
+    A.step = c->step;
+    const int t = c->strip.threads, cols = strip_cols(c->P, t), out = strip_out(c->P, t, c->strip.steps);
+    const int halo = strip_halo(c->strip.steps);
+    const dim3 g(strip_groups(c)), b(t);
+    auto go = [&](auto cap) {
+        constexpr int CAP = decltype(cap)::value;
+        if (reduce) hipLaunchKernelGGL((k_strip<T, CAP, true>), g, b, 0, s, A, cols, out, halo, n);
+        else hipLaunchKernelGGL((k_strip<T, CAP, false>), g, b, 0, s, A, cols, out, halo, n);
+    };
+    if (t <= 256) go(std::integral_constant<int, 256>());
+    else if (t <= 512) go(std::integral_constant<int, 512>());
+    else go(std::integral_constant<int, 1024>());
+    return hip_ok(hipGetLastError(), "k_strip launch");
 }
 
 bool launch_record_pair(lbm_ctx* c, void* rec, hipStream_t s)
@@ -867,6 +908,8 @@ int init_ctx(lbm_ctx* c, const lbm_params* p, void* f_a, void* f_b, void* ws, si
     c->red = (double*)(c->ws + orr);
     c->hist_count = 0;
     c->shape = two_step_shape(*p);
+    // the automatic variant only: an explicit one, or a named tile height, runs what it names
+    c->strip = p->kernel_variant == LBM_VARIANT_AUTO && p->tile_rows == 0 ? strip_plan(1, p) : StripPlan{0, 0};
     fill_args(c);
     hipStream_t s = (hipStream_t)stream;
     const unsigned init_err[2] = {0u, 0xffffffffu};
@@ -1041,6 +1084,25 @@ int lbm_step(lbm_ctx* c, int64_t nsteps, void* stream)
                                        hipMemcpyDeviceToDevice, s),
                         "checkpoint copy"))
                 return LBM_EHIP;
+        }
+        // (adjoint forwards, which record or checkpoint, take the steps that their recomputation takes)
+        if (c->strip.threads && !c->rec_all && c->ckpt_K == 0) {
+            // up to the next reducing step, in launches of equal length
+            const int64_t to_red = re > 0 ? (re - c->step % re) % re + 1 : nsteps;
+            const int64_t todo = to_red < nsteps - k ? to_red : nsteps - k;
+            const int64_t launches = (todo + c->strip.steps - 1) / c->strip.steps;
+            const int n = (int)((todo + launches - 1) / launches);
+            const bool last = re > 0 && (c->step + n - 1) % re == 0;
+            if (!(f32 ? launch_strip<float>(c, n, last, s) : launch_strip<double>(c, n, last, s))) return LBM_EHIP;
+            if (last) {
+                double* row = c->hist + 4 * (c->hist_count % kHistCap);
+                if (!launch_reduce_n(c, strip_groups(c), row, (long long)c->step + n - 1, 1, s)) return LBM_EHIP;
+                c->hist_count++;
+            }
+            c->cur ^= 1;
+            c->step += n;
+            k += n - 1;
+            continue;
         }
         const bool red = re > 0 && (c->step % re) == 0;
         void* rec = c->rec_all ? record_slot(c, c->step) : nullptr;
