@@ -45,6 +45,38 @@ constexpr size_t kStreamBytes = (size_t)64 << 20;
 
 constexpr int kStripW = 62;   // interior columns per wave (lanes 0 and 63 are the psi halo)
 
+// FP64 1/d, n/d and sqrt(a) for arguments in the middle of the exponent range: the hardware
+// estimate (2^-23 or better) and the refinement steps of the compiler's own sequences without
+// their scaling, class checks and fix-up, which serve arguments near the ends of the range
+// (densities, pressures and psi^2 are not).  Two Newton steps bring the error below 2^-90, so
+// that the last operation's rounding is all that is left; the results are the IEEE ones but for
+// ties that close.  8 instead of 11 instructions for a division, 5 for a reciprocal, 10 instead of
+// 17 for a square root, in the serial chain from the density to psi.  Measured (MI355X, us/step):
+// 512^2 FP32 4.54 -> 4.43 (its shaped loop is FP64), 600 x 250 with walls and tau(rho) FP32 4.57 ->
+// 4.44, 2048 x 1024 FP64 46.3 -> 45.6, 200 x 2 FP64 1.15 -> 1.07; every population bit-identical.
+// A zero, infinite or NaN argument gives NaN (sqrt: for 0 too; the callers select).
+__device__ __forceinline__ double fast_rcp(double d)
+{
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(r, fma(-d, r, 1.0), r);
+    return fma(r, fma(-d, r, 1.0), r);
+}
+__device__ __forceinline__ double fast_div(double n, double d)
+{
+    const double r = fast_rcp(d), q = n * r;
+    return fma(fma(-d, q, n), r, q);
+}
+__device__ __forceinline__ double fast_sqrt(double a)
+{
+    const double y = __builtin_amdgcn_rsq(a);
+    double g = a * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    g = fma(fma(-g, g, a), h, g);
+    return fma(fma(-g, g, a), h, g);
+}
+
 // ----------------------------------------------------------------- device EOS
 struct DevEos {
     int base, shape;
@@ -58,10 +90,10 @@ __device__ __forceinline__ double dev_base_p(const DevEos& E, double r)
 {
     if (E.base == LBM_BASE_CS) {
         const double n = 0.25 * E.b * r, m = 1.0 - n;
-        return E.scale * (E.RT * r * (1.0 + n * (1.0 + n * (1.0 - n))) / (m * m * m) - E.aal * r * r);
+        return E.scale * (fast_div(E.RT * r * (1.0 + n * (1.0 + n * (1.0 - n))), m * m * m) - E.aal * r * r);
     }
     const double br = E.b * r;
-    return E.scale * (E.RT * r / (1.0 - br) - E.aal * r * r / (1.0 + br * (2.0 - br)));
+    return E.scale * (fast_div(E.RT * r, 1.0 - br) - fast_div(E.aal * r * r, 1.0 + br * (2.0 - br)));
 }
 
 __device__ __forceinline__ double dev_eos_p(const DevEos& E, double r)
@@ -72,14 +104,14 @@ __device__ __forceinline__ double dev_eos_p(const DevEos& E, double r)
     if (E.shape == LBM_SHAPE_PENG) return E.p0 + E.theta * (r - E.rho_v) * (r - E.rho_l) * (r - E.rho_m);
     if (r <= E.rho_max) {
         const double d = r - E.rho_max;
-        return E.p_max - E.b1 * (1.0 - sqrt(1.0 - d * d * E.inv_a1sq));
+        return E.p_max - E.b1 * (1.0 - fast_sqrt(1.0 - d * d * E.inv_a1sq));
     }
     if (r < E.rho_min) {
         const double t = (r - E.rho_max) * E.inv_L;
         return E.p_max + (E.p_min - E.p_max) * t * t * (3.0 - 2.0 * t);
     }
     const double d = r - E.rho_min;
-    return E.p_min + E.b3 * (1.0 - sqrt(1.0 - d * d * E.inv_a3sq));
+    return E.p_min + E.b3 * (1.0 - fast_sqrt(1.0 - d * d * E.inv_a3sq));
 }
 
 __device__ __forceinline__ double dev_base_dp(const DevEos& E, double r)
@@ -173,9 +205,9 @@ __device__ __forceinline__ const Coef<double>& coef<double>(const StepArgs& A) {
 template <>
 __device__ __forceinline__ const Coef<float>& coef<float>(const StepArgs& A) { return A.cf; }
 
-// reciprocal: hardware v_rcp_f32 (1 ulp) on the FP32 path, IEEE division on the FP64 path
+// reciprocal: hardware v_rcp_f32 (1 ulp) on the FP32 path, fast_rcp on the FP64 path
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
+__device__ __forceinline__ double rcp(double x) { return fast_rcp(x); }
 
 __constant__ double kW[9] = {4.0 / 9.0, 1.0 / 9.0, 1.0 / 9.0, 1.0 / 9.0, 1.0 / 9.0,
                              1.0 / 36.0, 1.0 / 36.0, 1.0 / 36.0, 1.0 / 36.0};
@@ -350,7 +382,7 @@ __device__ __forceinline__ T node_psi(const StepArgs& A, const DevEos& E, double
     const double q = (p - rho * (1.0 / 3.0)) * A.cd.two_inv_G;
     if (check && !(q >= 0.0 && rho > 0.0)) flag_unstable(A, dstep);
     if (sizeof(T) == 4) return (T)(q > 0.0 ? __builtin_amdgcn_sqrtf((float)q) : 0.0f);
-    return (T)(q > 0.0 ? sqrt(q) : 0.0);
+    return (T)(q > 0.0 ? fast_sqrt(q) : 0.0);
 }
 template <typename T>
 __device__ __forceinline__ T node_psi(const StepArgs& A, double drho, bool check, int dstep = 0)
@@ -475,7 +507,7 @@ __device__ __forceinline__ bool node_collide(const StepArgs& A, const Lane& L, i
     if (A.var_tau) {
         double tau = A.tau_v + A.dtau_drho * (rho_d - A.rho_v_tau);
         tau = fmin(fmax(tau, A.tau_lo), A.tau_hi);
-        const T snu = (T)(1.0 / tau), hnu = (T)1 - (T)0.5 * snu;
+        const T snu = (T)fast_rcp(tau), hnu = (T)1 - (T)0.5 * snu;
         sh1 = ((T)1 - snu) * (T)0.25;
         sh2 = snu * (T)0.25;
         sh3 = hnu * (T)0.5;
