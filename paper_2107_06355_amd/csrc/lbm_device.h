@@ -86,9 +86,11 @@ struct DevEos {
     float fRT, faal, fb, fscale, fk_vap, fdP;  // the bulk-branch constants rounded to FP32 (FP32 path)
 };
 
-__device__ __forceinline__ double dev_base_p(const DevEos& E, double r)
+// base, shape: E's own, apart from the record so that a caller whose record lies in LDS can give
+// them from scalar registers (a scalar branch instead of a lane mask that waits for an LDS read)
+__device__ __forceinline__ double dev_base_p(const DevEos& E, int base, double r)
 {
-    if (E.base == LBM_BASE_CS) {
+    if (base == LBM_BASE_CS) {
         const double n = 0.25 * E.b * r, m = 1.0 - n;
         return E.scale * (fast_div(E.RT * r * (1.0 + n * (1.0 + n * (1.0 - n))), m * m * m) - E.aal * r * r);
     }
@@ -96,12 +98,12 @@ __device__ __forceinline__ double dev_base_p(const DevEos& E, double r)
     return E.scale * (fast_div(E.RT * r, 1.0 - br) - fast_div(E.aal * r * r, 1.0 + br * (2.0 - br)));
 }
 
-__device__ __forceinline__ double dev_eos_p(const DevEos& E, double r)
+__device__ __forceinline__ double dev_eos_p(const DevEos& E, int base, int shape, double r)
 {
-    if (E.shape == LBM_SHAPE_NONE) return dev_base_p(E, r);
-    if (r <= E.rho_v) return E.k_vap * dev_base_p(E, r);
-    if (r >= E.rho_l) return dev_base_p(E, r) + E.dP;
-    if (E.shape == LBM_SHAPE_PENG) return E.p0 + E.theta * (r - E.rho_v) * (r - E.rho_l) * (r - E.rho_m);
+    if (shape == LBM_SHAPE_NONE) return dev_base_p(E, base, r);
+    if (r <= E.rho_v) return E.k_vap * dev_base_p(E, base, r);
+    if (r >= E.rho_l) return dev_base_p(E, base, r) + E.dP;
+    if (shape == LBM_SHAPE_PENG) return E.p0 + E.theta * (r - E.rho_v) * (r - E.rho_l) * (r - E.rho_m);
     if (r <= E.rho_max) {
         const double d = r - E.rho_max;
         return E.p_max - E.b1 * (1.0 - fast_sqrt(1.0 - d * d * E.inv_a1sq));
@@ -113,6 +115,8 @@ __device__ __forceinline__ double dev_eos_p(const DevEos& E, double r)
     const double d = r - E.rho_min;
     return E.p_min + E.b3 * (1.0 - fast_sqrt(1.0 - d * d * E.inv_a3sq));
 }
+
+__device__ __forceinline__ double dev_eos_p(const DevEos& E, double r) { return dev_eos_p(E, E.base, E.shape, r); }
 
 __device__ __forceinline__ double dev_base_dp(const DevEos& E, double r)
 {
@@ -338,9 +342,9 @@ __device__ __forceinline__ void flag_unstable(const StepArgs& A, int dstep = 0)
 }
 
 // base EOS in FP32 (bulk branches of the FP32 path)
-__device__ __forceinline__ float dev_base_pf(const DevEos& E, float r)
+__device__ __forceinline__ float dev_base_pf(const DevEos& E, int base, float r)
 {
-    if (E.base == LBM_BASE_CS) {
+    if (base == LBM_BASE_CS) {
         const float n = 0.25f * E.fb * r, m = 1.0f - n;
         return E.fscale *
                (E.fRT * r * (1.0f + n * (1.0f + n * (1.0f - n))) * __builtin_amdgcn_rcpf(m * m * m) - E.faal * r * r);
@@ -366,19 +370,21 @@ __device__ __forceinline__ float dev_base_dpf(const DevEos& E, float r)
 // FP64 path: everything in FP64.  FP32 path: the bulk vapor/liquid branches in
 // FP32, the shaped loop between rho_v and rho_l (the branch junctions) in FP64;
 // the square root is the hardware one (within 1 ulp, no correction sequence).
+// base, shape: those of E (scalar values where the caller has them: see dev_base_p).
 template <typename T>
-__device__ __forceinline__ T node_psi(const StepArgs& A, const DevEos& E, double drho, bool check, int dstep = 0)
+__device__ __forceinline__ T node_psi(const StepArgs& A, const DevEos& E, int base, int shape, double drho, bool check,
+                                      int dstep = 0)
 {
     const double rho = A.rho_ref + drho;
-    if (sizeof(T) == 4 && E.shape != LBM_SHAPE_NONE && (rho <= E.rho_v || rho >= E.rho_l)) {
+    if (sizeof(T) == 4 && shape != LBM_SHAPE_NONE && (rho <= E.rho_v || rho >= E.rho_l)) {
         const float r = (float)rho;
-        const float pb = dev_base_pf(E, r);
+        const float pb = dev_base_pf(E, base, r);
         const float p = rho <= E.rho_v ? E.fk_vap * pb : pb + E.fdP;
         const float q = (p - r * (1.0f / 3.0f)) * A.cf.two_inv_G;
         if (check && !(q >= 0.0f && r > 0.0f)) flag_unstable(A, dstep);
         return (T)(q > 0.0f ? __builtin_amdgcn_sqrtf(q) : 0.0f);
     }
-    const double p = dev_eos_p(E, rho);
+    const double p = dev_eos_p(E, base, shape, rho);
     const double q = (p - rho * (1.0 / 3.0)) * A.cd.two_inv_G;
     if (check && !(q >= 0.0 && rho > 0.0)) flag_unstable(A, dstep);
     if (sizeof(T) == 4) return (T)(q > 0.0 ? __builtin_amdgcn_sqrtf((float)q) : 0.0f);
@@ -387,7 +393,7 @@ __device__ __forceinline__ T node_psi(const StepArgs& A, const DevEos& E, double
 template <typename T>
 __device__ __forceinline__ T node_psi(const StepArgs& A, double drho, bool check, int dstep = 0)
 {
-    return node_psi<T>(A, A.eos, drho, check, dstep);
+    return node_psi<T>(A, A.eos, A.eos.base, A.eos.shape, drho, check, dstep);
 }
 
 // 32-bit DPP move of each half of a double; lanes without a source (or outside the row mask
@@ -847,7 +853,7 @@ __device__ __forceinline__ void step2_tile(const StepArgs& A, int strip, int ban
     if (ring3) {
         if (fluid) {
             dr = node_drho<T>(R.g0, R.g);
-            ps = node_psi<T>(A, S.eos, dr, true);
+            ps = node_psi<T>(A, S.eos, A.eos.base, A.eos.shape, dr, true);
         } else {
             ps = ghost;
         }
@@ -899,7 +905,7 @@ __device__ __forceinline__ void step2_tile(const StepArgs& A, int strip, int ban
             R.g[8] = smv[5][q][l];
         }
         dr = node_drho<T>(R.g0, R.g);
-        ps = node_psi<T>(A, S.eos, dr, true, 1);
+        ps = node_psi<T>(A, S.eos, A.eos.base, A.eos.shape, dr, true, 1);
         sps[k][l] = ps;
     } else if (walls && dk <= 1 && dl <= 1) {
         sps[k][l] = ghost;
@@ -996,7 +1002,9 @@ __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, in
 
     // 1. step t: pull, rho, psi.  The EOS record is copied to LDS while the pull is in
     //    flight: psi reads it there in phases 1 and 3, instead of the launch holding it in
-    //    scalar registers (which spills them to vector lanes at this occupancy).
+    //    scalar registers (which spills them to vector lanes at this occupancy).  Even its
+    //    base and shape: two scalar registers more spilled 4 (8192^2 FP32 567 -> 573 us/step;
+    //    the one-row kernel has room for them and gains 1.3% at 512^2).
     if (threadIdx.x == 0) S.eos = A.eos;
     Row<T> R[RPW];
     double dr[RPW];
@@ -1018,7 +1026,7 @@ __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, in
         if (dk_of(kk) <= 3 && dl <= 3) {
             if (fluid_of(r)) {
                 dr[j] = node_drho<T>(R[j].g0, R[j].g);
-                ps[j] = node_psi<T>(A, S.eos, dr[j], true);
+                ps[j] = node_psi<T>(A, S.eos, S.eos.base, S.eos.shape, dr[j], true);
             } else {
                 ps[j] = ghost_of(r);
             }
@@ -1078,7 +1086,7 @@ __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, in
                 R[j].g[8] = smv[5][q][l];
             }
             dr[j] = node_drho<T>(R[j].g0, R[j].g);
-            ps[j] = node_psi<T>(A, S.eos, dr[j], true, 1);
+            ps[j] = node_psi<T>(A, S.eos, S.eos.base, S.eos.shape, dr[j], true, 1);
             sps[kk][l] = ps[j];
         } else if (walls && dk <= 1 && dl <= 1) {
             sps[kk][l] = ghost_of(r);

@@ -150,7 +150,7 @@ __device__ __forceinline__ void strip_steps(const StepArgs& A, const void* src, 
         const int left = nsteps - 1 - s;
         // columns beyond 2 left + 1 have used up their neighbours: whatever they hold is not read
         // by a column that has not, and is not checked
-        const T ps = node_psi<T>(A, S.eos, dr, row && d <= 2 * left + 1, step + s);
+        const T ps = node_psi<T>(A, S.eos, A.eos.base, A.eos.shape, dr, row && d <= 2 * left + 1, step + s);
         S.ps[n] = ps;
         __syncthreads();
         T Ftx, Fty;
