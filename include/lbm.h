@@ -155,11 +155,12 @@ int lbm_layout(const lbm_params* p, int* ld_out, size_t* pop_bytes_out, size_t* 
 
 /* Which step-kernel decomposition the parameters select (the automatic
  * choice resolved), the rows per band or block, and the wavefront count; for
- * BLOCK2 the output rows of a two-step tile and the wavefronts of its
+ * BLOCK2 the output rows of the fixed rule's two-step tile and the wavefronts of its
  * workgroup (rows + 6 = wavefronts x rows per wavefront; two rows per
  * wavefront when rows + 6 < 2 x wavefronts + 1, i.e. rows > wavefronts - 6).
- * With tile_rows = -1 this is the shape before lbm_init times the candidates:
- * lbm_tile_shape reports the one a context runs.  LBM_VARIANT_AA: 4 rows and
+ * A context may run another height: the one lbm_init times for tile_rows = -1, or
+ * for tile_rows = 0 one that fills the chip better with this lattice's tiles;
+ * lbm_tile_shape reports it.  LBM_VARIANT_AA: 4 rows and
  * 4 wavefronts per workgroup. */
 int lbm_describe(const lbm_params* p, int* variant_out, int* band_rows_out, int* waves_out);
 

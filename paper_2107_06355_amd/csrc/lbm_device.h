@@ -713,6 +713,48 @@ inline TwoStepShape two_step_shape(const lbm_params& p)
         return {k2rWavesOf<float>, k2rRowsOf<float>, true};
     return {k2WavesOf<float>, k2WavesOf<float> - 6, false};
 }
+// The shape a context runs when the caller leaves it to the library (tile_rows 0, and -1 where
+// there is nothing to time): two_step_shape, or another height where it fills the chip better.
+//
+// Few tiles: n = ceil(tiles / 256) workgroups run on the busiest CU, two at a time, so a launch
+// takes about 2 us and then a pair's or a single one's time, which grow with the rows: FP64 2.9 +
+// 0.8 h and 3.1 + 0.48 h us, FP32 3.8 + 0.32 h and 3.1 + 0.215 h, FP32 one-row tiles 6.5 and 4.4.
+// The height with the least of it runs (fitted to 44 lattices from 128^2 to 1000 x 600, periodic
+// and walled; us per launch of the fixed rule -> this one: 256 x 200 FP64 9.8 -> 7.6, 600 x 250
+// FP64 11.6 -> 9.4, FP32 8.2 -> 7.9, 700^2 FP32 15.4 -> 13.2); the fixed rule's height stays unless
+// another is 3% better.  Past about a thousand tiles the estimate no longer tells heights apart
+// (1000 x 600 FP64, 1080 tiles: 8 rows 28.9, 10 rows 27.6), and the fixed rule holds.
+// Many tiles, FP32: two rows per wave pay from 2000 18-row tiles on (48 more lattices; 2353 x 1425
+// 70.4 -> 62.8, 2048 x 1024 with walls 44.8 -> 43.5); below 2600 17 rows, which leave a fuller last
+// round there than 18 (1613 x 1451 with walls: 48.9 one-row, 47.8 and 46.9).
+constexpr int kFewTiles[2] = {1000, 1100};  // FP64, FP32
+inline TwoStepShape run_shape(const lbm_params& p)
+{
+    TwoStepShape best = two_step_shape(p);
+    if (p.tile_rows > 0) return best;
+    const bool f32 = p.prec == LBM_FP32_SHIFTED;
+    const long long strips = (p.nx + k2Cols - 1) / k2Cols;
+    auto tiles = [&](int h) { return strips * ((p.ny + h - 1) / h); };
+    if (tiles(10) > kFewTiles[f32]) {
+        const long long t = f32 ? tiles(k2rRowsOf<float>) : 0;
+        if (t >= 2000) return shape_of_height(true, t < 2600 ? 17 : 18);
+        return best;
+    }
+    double best_us = 0.0;
+    const int heights[2][6] = {{10, 8, 6, 5, 0, 0}, {10, 12, 14, 16, 18, 0}};
+    for (const int* h = heights[f32]; *h; ++h) {
+        const TwoStepShape sh = shape_of_height(f32, *h);
+        const long long n = (tiles(*h) + 255) / 256;
+        const double pair = !f32 ? 2.9 + 0.8 * *h : (sh.rows2 ? 3.8 + 0.32 * *h : 6.5);
+        const double single = !f32 ? 3.1 + 0.48 * *h : (sh.rows2 ? 3.1 + 0.215 * *h : 4.4);
+        const double us = (double)(n / 2) * pair + (double)(n % 2) * single;
+        if (h == heights[f32] || us < best_us) {
+            best = sh;
+            best_us = h == heights[f32] ? 0.97 * us : us;  // the first is the fixed rule's
+        }
+    }
+    return best;
+}
 // Candidates lbm_init times for tile_rows = -1, the library's choice first.  How the tiles of a
 // launch fill the chip's rounds of workgroups, its XCDs and its L2s makes the best height
 // depend on the lattice by up to 9% (measured on MI355X, FP32: the walled 2048 x 1024 impact

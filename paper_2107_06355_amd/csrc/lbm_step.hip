@@ -907,7 +907,7 @@ int init_ctx(lbm_ctx* c, const lbm_params* p, void* f_a, void* f_b, void* ws, si
     c->hist = (double*)(c->ws + oh);
     c->red = (double*)(c->ws + orr);
     c->hist_count = 0;
-    c->shape = two_step_shape(*p);
+    c->shape = run_shape(*p);
     // the automatic variant only: an explicit one, or a named tile height, runs what it names
     c->strip = p->kernel_variant == LBM_VARIANT_AUTO && p->tile_rows == 0 ? strip_plan(1, p) : StripPlan{0, 0};
     fill_args(c);
