@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -487,15 +488,18 @@ int partial_slots(const lbm_params& p)
     return n;
 }
 
-size_t ws_layout(int nwork, size_t* off_part, size_t* off_hist, size_t* off_red)
+// offset in the workspace's first 256 bytes of lbm_macros' sums, behind the error word: one copy
+// to the host brings both
+constexpr size_t kRedOff = 64;
+
+size_t ws_layout(int nwork, size_t* off_part, size_t* off_hist)
 {
-    size_t o = 256;  // error word
+    size_t o = 256;  // error word, sums of lbm_macros
     *off_part = o;
     o += ((size_t)nwork * 3 * sizeof(double) + 255) & ~(size_t)255;
     o += (size_t)kRedBlocks * 3 * sizeof(double);  // per-block sums of the two-pass reduction
     *off_hist = o;
     o += (size_t)kHistCap * 4 * sizeof(double);
-    *off_red = o;
     o += 256;
     return o;
 }
@@ -761,8 +765,8 @@ int lbm_layout(const lbm_params* p, int* ld_out, size_t* pop_bytes_out, size_t* 
     const size_t bytes = p->prec == LBM_FP32_SHIFTED ? plane * (8 * sizeof(float) + sizeof(double)) : plane * 9 * sizeof(double);
     int strips, seg_h, nseg, blk;
     decompose(*p, &strips, &seg_h, &nseg, &blk);
-    size_t a, b, d;
-    size_t ws = ws_layout(partial_slots(*p), &a, &b, &d);
+    size_t a, b;
+    size_t ws = ws_layout(partial_slots(*p), &a, &b);
     if (resolve_variant(*p) == LBM_VARIANT_AA) ws += aa_psi_bytes(*p, ld);  // the psi plane
     if (ld_out) *ld_out = ld;
     if (pop_bytes_out) *pop_bytes_out = bytes;
@@ -898,14 +902,14 @@ int init_ctx(lbm_ctx* c, const lbm_params* p, void* f_a, void* f_b, void* ws, si
     c->step = 0;
     c->ws = (char*)ws;
     c->ws_bytes = ws_bytes;
-    size_t op, oh, orr;
-    const size_t ws_base = ws_layout(partial_slots(*p), &op, &oh, &orr);
+    size_t op, oh;
+    const size_t ws_base = ws_layout(partial_slots(*p), &op, &oh);
     c->aa_psi = c->aa ? c->ws + ws_base : nullptr;
     c->err = (unsigned*)c->ws;
     c->partials = (double*)(c->ws + op);
     c->redblk = (double*)(c->ws + oh - (size_t)kRedBlocks * 3 * sizeof(double));
     c->hist = (double*)(c->ws + oh);
-    c->red = (double*)(c->ws + orr);
+    c->red = (double*)(c->ws + kRedOff);
     c->hist_count = 0;
     c->shape = run_shape(*p);
     // the automatic variant only: an explicit one, or a named tile height, runs what it names
@@ -1150,6 +1154,16 @@ int lbm_step(lbm_ctx* c, int64_t nsteps, void* stream)
     return LBM_OK;
 }
 
+// LBM_EUNSTABLE and its message if the error word h (copied from the device) is set
+static int status_of(const unsigned h[2])
+{
+    if (!h[0]) return LBM_OK;
+    char buf[160];
+    std::snprintf(buf, sizeof(buf), "lbm: psi^2 < 0 or non-positive density first met at step %u", h[1]);
+    lbm_set_error(buf);
+    return LBM_EUNSTABLE;
+}
+
 int lbm_status_check(lbm_ctx* c, void* stream)
 {
     if (!c) return LBM_EINVAL;
@@ -1158,13 +1172,7 @@ int lbm_status_check(lbm_ctx* c, void* stream)
     if (!hip_ok(hipMemcpyAsync(h, c->err, sizeof(h), hipMemcpyDeviceToHost, s), "status copy") ||
         !hip_ok(hipStreamSynchronize(s), "status sync"))
         return LBM_EHIP;
-    if (h[0]) {
-        char buf[160];
-        std::snprintf(buf, sizeof(buf), "lbm: psi^2 < 0 or non-positive density first met at step %u", h[1]);
-        lbm_set_error(buf);
-        return LBM_EUNSTABLE;
-    }
-    return LBM_OK;
+    return status_of(h);
 }
 
 int lbm_macros(lbm_ctx* c, double* rho, double* ux, double* uy, double* psi, double* p, double* Fx, double* Fy,
@@ -1196,12 +1204,19 @@ int lbm_macros(lbm_ctx* c, double* rho, double* ux, double* uy, double* psi, dou
     }
     if (!hip_ok(hipGetLastError(), "k_step(macros) launch")) return LBM_EHIP;
     if (!c->aa && !launch_reduce(c, c->red, 0LL, 0, s)) return LBM_EHIP;
-    double h[3];
-    if (!hip_ok(hipMemcpyAsync(h, c->red, sizeof(h), hipMemcpyDeviceToHost, s), "macros copy") ||
+    // the sums and the error word in one copy and one wait (a copy to the host and its wait take
+    // about 20 us, most of the call on small lattices: 200 x 2 63 -> 43 us)
+    struct {
+        unsigned err[2];
+        char gap[kRedOff - 2 * sizeof(unsigned)];
+        double sums[3];
+    } h;
+    static_assert(offsetof(decltype(h), sums) == kRedOff, "as in the workspace");
+    if (!hip_ok(hipMemcpyAsync(&h, c->err, sizeof(h), hipMemcpyDeviceToHost, s), "macros copy") ||
         !hip_ok(hipStreamSynchronize(s), "macros sync"))
         return LBM_EHIP;
-    if (host_mass_mom) std::memcpy(host_mass_mom, h, sizeof(h));
-    return lbm_status_check(c, stream);
+    if (host_mass_mom) std::memcpy(host_mass_mom, h.sums, sizeof(h.sums));
+    return status_of(h.err);
 }
 
 int lbm_populations(lbm_ctx* c, double* f_out, void* stream)
@@ -1223,13 +1238,16 @@ int lbm_history(lbm_ctx* c, double* host_rows, int max_rows, int* n_out, void* s
     hipStream_t s = (hipStream_t)stream;
     const int64_t avail = c->hist_count < kHistCap ? c->hist_count : kHistCap;
     const int n = (int)(avail < max_rows ? avail : max_rows);
-    // newest n rows, oldest first
-    for (int k = 0; k < n; ++k) {
-        const int64_t idx = (c->hist_count - n + k) % kHistCap;
-        if (!hip_ok(hipMemcpyAsync(host_rows + 4 * k, c->hist + 4 * idx, 4 * sizeof(double), hipMemcpyDeviceToHost, s),
-                    "history copy"))
-            return LBM_EHIP;
-    }
+    // newest n rows, oldest first: the ring up to its end, then from its start
+    const int64_t first = (c->hist_count - n) % kHistCap;
+    const int tail = (int)(n < kHistCap - first ? n : kHistCap - first);
+    if ((tail > 0 && !hip_ok(hipMemcpyAsync(host_rows, c->hist + 4 * first, (size_t)tail * 4 * sizeof(double),
+                                            hipMemcpyDeviceToHost, s),
+                             "history copy")) ||
+        (n > tail && !hip_ok(hipMemcpyAsync(host_rows + 4 * tail, c->hist, (size_t)(n - tail) * 4 * sizeof(double),
+                                            hipMemcpyDeviceToHost, s),
+                             "history copy")))
+        return LBM_EHIP;
     if (!hip_ok(hipStreamSynchronize(s), "history sync")) return LBM_EHIP;
     if (n_out) *n_out = n;
     return LBM_OK;

@@ -435,11 +435,12 @@ class Batch:
     def macros(self):
         t = self.torch
         n = self.offsets[-1]
-        rho, ux, uy = (t.empty(n, dtype=t.float64, device=self.device) for _ in range(3))
+        fields = t.empty((3, n), dtype=t.float64, device=self.device)
+        rho, ux, uy = fields
         _check(load().lbm_macros_batched(self._h, rho.data_ptr(), ux.data_ptr(), uy.data_ptr(),
                                          C.c_void_p(self.stream.cuda_stream)), "lbm_macros_batched")
         out = []
-        r, u, v = rho.cpu().numpy(), ux.cpu().numpy(), uy.cpu().numpy()
+        r, u, v = fields.cpu().numpy()
         for b, (ny, nx) in enumerate(self.shapes):
             sl = slice(self.offsets[b], self.offsets[b + 1])
             out.append({"rho": r[sl].reshape(ny, nx), "ux": u[sl].reshape(ny, nx), "uy": v[sl].reshape(ny, nx)})
