@@ -1048,6 +1048,13 @@ __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, in
     //    base and shape: two scalar registers more spilled 4 (8192^2 FP32 567 -> 573 us/step;
     //    the one-row kernel has room for them and gains 1.3% at 512^2).
     if (threadIdx.x == 0) S.eos = A.eos;
+    // FP64 loads every row, one that is not needed (or is solid) from a row that is there: a
+    // wave's loads are then the same on every path, so its first row waits for its own loads
+    // only and its node_psi runs while the second row's arrive (700^2 11.8 -> 11.1, 1024^2
+    // 20.4 -> 19.4, 2048^2 81.5 -> 80.4 us/step; 6144^2, bound by HBM, unchanged).  FP32 keeps
+    // the guards: 1600^2 24.5 -> 23.8 without them, but 600 x 250, whose lower tiles have rows
+    // to spare, 4.18 -> 4.24 and 8192^2 612 -> 617.
+    constexpr bool kAllRows = sizeof(T) == 8;
     Row<T> R[RPW];
     double dr[RPW];
     T ps[RPW];
@@ -1056,8 +1063,11 @@ __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, in
         const int kk = k + j * NW, r = r_of(kk);
         dr[j] = 0.0;
         ps[j] = (T)0;
-        if (dk_of(kk) <= 3 && dl <= 3 && fluid_of(r)) {
-            const View<T> V = make_view<T>(A.src, A.plane);
+        const View<T> V = make_view<T>(A.src, A.plane);
+        if constexpr (kAllRows) {
+            const int rl = dk_of(kk) > 3 ? y0 : (walls ? min(max(r, 0), A.ny - 1) : rw_of(r));
+            pull<T>(V, A, L.x, L.xm, L.xp, rl, R[j].g0, R[j].g);
+        } else if (dk_of(kk) <= 3 && dl <= 3 && fluid_of(r)) {
             pull<T>(V, A, L.x, L.xm, L.xp, rw_of(r), R[j].g0, R[j].g);
         }
     }
