@@ -264,11 +264,11 @@ __device__ __forceinline__ void knot_adjoint(const DevEos& E, double rho, double
     // registers
     double pmax = 0, pmin = 0, rmax = 0, rmin = 0, b1 = 0, a1 = 0, b3 = 0, a3 = 0;
     if (rho <= E.rho_max) {
-        const double dd = rho - E.rho_max, sq = sqrt(1.0 - dd * dd * E.inv_a1sq);
+        const double dd = rho - E.rho_max, sq = fast_sqrt(1.0 - dd * dd * E.inv_a1sq);
         pmax = P;
         b1 = -P * (1.0 - sq);
-        a1 = P * E.b1 * dd * dd * E.inv_a1sq * E.inv_a1sq / (2.0 * sq);
-        rmax = P * E.b1 * dd * E.inv_a1sq / sq;
+        a1 = fast_div(P * E.b1 * dd * dd * E.inv_a1sq * E.inv_a1sq, 2.0 * sq);
+        rmax = fast_div(P * E.b1 * dd * E.inv_a1sq, sq);
     } else if (rho < E.rho_min) {
         const double tt = (rho - E.rho_max) * E.inv_L;
         const double h = tt * tt * (3.0 - 2.0 * tt), hp = 6.0 * tt * (1.0 - tt);
@@ -277,11 +277,11 @@ __device__ __forceinline__ void knot_adjoint(const DevEos& E, double rho, double
         rmax = P * (E.p_min - E.p_max) * hp * (tt - 1.0) * E.inv_L;
         rmin = P * (E.p_min - E.p_max) * hp * (-tt) * E.inv_L;
     } else {
-        const double dd = rho - E.rho_min, sq = sqrt(1.0 - dd * dd * E.inv_a3sq);
+        const double dd = rho - E.rho_min, sq = fast_sqrt(1.0 - dd * dd * E.inv_a3sq);
         pmin = P;
         b3 = P * (1.0 - sq);
-        a3 = -P * E.b3 * dd * dd * E.inv_a3sq * E.inv_a3sq / (2.0 * sq);
-        rmin = -P * E.b3 * dd * E.inv_a3sq / sq;
+        a3 = fast_div(-P * E.b3 * dd * dd * E.inv_a3sq * E.inv_a3sq, 2.0 * sq);
+        rmin = fast_div(-P * E.b3 * dd * E.inv_a3sq, sq);
     }
     v[A_PMAX] += pmax;
     v[A_PMIN] += pmin;

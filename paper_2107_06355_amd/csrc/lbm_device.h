@@ -53,7 +53,8 @@ constexpr int kStripW = 62;   // interior columns per wave (lanes 0 and 63 are t
 // ties that close.  8 instead of 11 instructions for a division, 5 for a reciprocal, 10 instead of
 // 17 for a square root, in the serial chain from the density to psi.  Measured (MI355X, us/step):
 // 512^2 FP32 4.54 -> 4.43 (its shaped loop is FP64), 600 x 250 with walls and tau(rho) FP32 4.57 ->
-// 4.44, 2048 x 1024 FP64 46.3 -> 45.6, 200 x 2 FP64 1.15 -> 1.07; every population bit-identical.
+// 4.44, 2048 x 1024 FP64 46.3 -> 45.6, 200 x 2 FP64 1.15 -> 1.07; the adjoint's dp/drho: two transposed steps at 512^2 FP32
+// 17.4 -> 16.7, 256 x 200 FP64 11.3 -> 11.1; every population and gradient bit-identical.
 // A zero, infinite or NaN argument gives NaN (sqrt: for 0 too; the callers select).
 __device__ __forceinline__ double fast_rcp(double d)
 {
@@ -123,10 +124,10 @@ __device__ __forceinline__ double dev_base_dp(const DevEos& E, double r)
     if (E.base == LBM_BASE_CS) {
         const double n = 0.25 * E.b * r, m = 1.0 - n;
         const double m2 = m * m;
-        return E.scale * (E.RT * (1.0 + n * (4.0 + n * (4.0 + n * (-4.0 + n)))) / (m2 * m2) - 2.0 * E.aal * r);
+        return E.scale * (fast_div(E.RT * (1.0 + n * (4.0 + n * (4.0 + n * (-4.0 + n)))), m2 * m2) - 2.0 * E.aal * r);
     }
     const double br = E.b * r, m = 1.0 - br, D = 1.0 + br * (2.0 - br);
-    return E.scale * (E.RT / (m * m) - 2.0 * E.aal * r * (1.0 + br) / (D * D));
+    return E.scale * (fast_div(E.RT, m * m) - fast_div(2.0 * E.aal * r * (1.0 + br), D * D));
 }
 
 // dp/drho of the shaped EOS (FP64)
@@ -141,14 +142,14 @@ __device__ __forceinline__ double dev_eos_dp(const DevEos& E, double r)
     }
     if (r <= E.rho_max) {
         const double d = r - E.rho_max;
-        return -E.b1 * d * E.inv_a1sq / sqrt(1.0 - d * d * E.inv_a1sq);
+        return fast_div(-E.b1 * d * E.inv_a1sq, fast_sqrt(1.0 - d * d * E.inv_a1sq));
     }
     if (r < E.rho_min) {
         const double t = (r - E.rho_max) * E.inv_L;
         return (E.p_min - E.p_max) * 6.0 * t * (1.0 - t) * E.inv_L;
     }
     const double d = r - E.rho_min;
-    return E.b3 * d * E.inv_a3sq / sqrt(1.0 - d * d * E.inv_a3sq);
+    return fast_div(E.b3 * d * E.inv_a3sq, fast_sqrt(1.0 - d * d * E.inv_a3sq));
 }
 
 // ----------------------------------------------------------------- kernel arguments
