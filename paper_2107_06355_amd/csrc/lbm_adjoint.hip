@@ -46,6 +46,7 @@ struct AdjArgs {
     double* acc;         // [blocks][kAcc] running sums
     int strips;          // column strips of kAdjW outputs
     int strips2;         // column strips of kAdj2W outputs (two steps per launch)
+    int xcd;             // the two-step tiles of one XCD are neighbours (adj2_xcd)
     size_t lplane, rplane;
     double c_e, c_q;     // 1/(tau_e - 1/2), 1/(tau_eps - 1/2) of Eq. LiFS
     double inv_G;
@@ -482,6 +483,7 @@ template <typename T, bool NT, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 4))) void k_adj2_blk(AdjArgs A)
 {
     constexpr int R = Adj2Lds<NW>::R;
+    static_assert(kAcc <= NW, "one wave per accumulator in the workgroup sum");
     __shared__ T sfx[NW][64], sfy[NW][64];
     // lambda^t, populations 1..8 ([i - 1][wave][lane]); after the second step the same
     // memory holds the workgroup sum's staging ([accumulator][output row][lane])
@@ -491,7 +493,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     const StepArgs& S = A.S;
     const int lane = threadIdx.x & 63;
     const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int strip = blockIdx.x % A.strips2, band = blockIdx.x / A.strips2;
+    // the grid is padded to a multiple of 8; XCD-contiguous tiles where adj2_xcd says so
+    const int tile = A.xcd ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) : (int)blockIdx.x;
+    const int strip = tile % A.strips2, band = tile / A.strips2;
+    if (band * R >= S.ny) return;  // whole workgroup leaves together
     const int xs = strip * kAdj2W - 3 + lane;  // unwrapped column of this lane
     // xs lies in [-3, nx + 60] and y in [-3, ny + NW - 5]: one wrap each way on lattices at
     // least 64 wide and NW tall, remainders otherwise
@@ -501,7 +506,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     const int yw = S.walls ? (y < 0 ? 0 : (y >= S.ny ? S.ny - 1 : y))
                            : (S.ny >= NW ? wrapx(y, S.ny) : ((y % S.ny) + S.ny) % S.ny);
     const bool own = k >= 3 && k < 3 + R && y < S.ny && lane >= 3 && lane < 3 + kAdj2W && xs < S.nx;
-    const double acc_prev = (k < kAcc && lane == kTotalLane) ? A.acc[(size_t)blockIdx.x * kAcc + k] : 0.0;
+    const double acc_prev = (k < kAcc && lane == kTotalLane) ? A.acc[(size_t)tile * kAcc + k] : 0.0;
     // what the first step leaves for the parameter sums of this node
     T a_psi = 0, a_dpsi = 0, a_dr = 0, a_vG = 0, a_sig = 0;
 
@@ -593,7 +598,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
         double s = 0.0;
         for (int w = 0; w < R; ++w) s += red[k][w][lane];
         s = wave_total(s);
-        if (lane == kTotalLane) A.acc[(size_t)blockIdx.x * kAcc + k] = acc_prev + s;
+        if (lane == kTotalLane) A.acc[(size_t)tile * kAcc + k] = acc_prev + s;
     }
 }
 
@@ -721,25 +726,51 @@ void launch_adj_step(bool f32, bool nt, int blocks, hipStream_t s, const AdjArgs
     else hipLaunchKernelGGL((k_adj_blk<double, false>), g, b, 0, s, A);
 }
 
-constexpr int kAdj2Waves = 16;  // waves (rows) per workgroup of the two-step transposed kernel
-
-void launch_adj2_step(bool f32, bool nt, int blocks, hipStream_t s, const AdjArgs& A)
+// Two transposed steps by workgroups of `waves` waves (Adj2Lds: waves - 6 output rows each).  A
+// lattice of so few tiles takes at most 119k nodes, so its lambda is always stored streaming (nt).
+constexpr int kAdj2Waves = 16;
+template <typename T>
+void launch_adj2(int waves, bool nt, int blocks, hipStream_t s, const AdjArgs& A)
 {
-    const dim3 g(blocks), b(64 * kAdj2Waves);
-    if (f32 && nt) hipLaunchKernelGGL((k_adj2_blk<float, true, kAdj2Waves>), g, b, 0, s, A);
-    else if (f32) hipLaunchKernelGGL((k_adj2_blk<float, false, kAdj2Waves>), g, b, 0, s, A);
-    else if (nt) hipLaunchKernelGGL((k_adj2_blk<double, true, kAdj2Waves>), g, b, 0, s, A);
-    else hipLaunchKernelGGL((k_adj2_blk<double, false, kAdj2Waves>), g, b, 0, s, A);
+    const dim3 g((blocks + 7) / 8 * 8), b(64 * waves);
+    if (waves == 10) hipLaunchKernelGGL((k_adj2_blk<T, true, 10>), g, b, 0, s, A);
+    else if (waves == 12) hipLaunchKernelGGL((k_adj2_blk<T, true, 12>), g, b, 0, s, A);
+    else if (waves == 14) hipLaunchKernelGGL((k_adj2_blk<T, true, 14>), g, b, 0, s, A);
+    else if (nt) hipLaunchKernelGGL((k_adj2_blk<T, true, kAdj2Waves>), g, b, 0, s, A);
+    else hipLaunchKernelGGL((k_adj2_blk<T, false, kAdj2Waves>), g, b, 0, s, A);
 }
 
 struct AdjLayout {
     size_t tsz, rec_bytes, off_fT, off_lam0, off_lam1, off_acc, total;
     int strips, blocks;    // one transposed step per launch
     int strips2, blocks2;  // two per launch
+    int waves2;            // waves per workgroup of the two-step kernel
     size_t nacc;           // accumulators: kAcc per workgroup of the larger grid
 };
 
-AdjLayout adj_layout(const lbm_params& p, int ld, size_t pop_bytes, int K)
+// Waves per workgroup of the two-step transposed kernel: the fewest whose tiles still get a
+// compute unit each.  A workgroup issues its waves' instructions on four SIMDs, and that is what
+// its time is (a launch of 100 workgroups takes as long as one of 250): 16 waves are four rows of
+// work per SIMD for 10 rows of output, 10 waves at most three for 4.  Measured (MI355X, us per
+// launch, 16 / 14 / 12 / 10 waves): 256 x 200 FP64 15.0 / 13.3 / 12.2 / 11.3, FP32 12.1 / 11.2 /
+// 10.7 / 9.6; beyond one tile per compute unit (350 x 300, 210 / 266 / 350 / 525 tiles) FP64
+// 15.5 / 22.0 / 20.9 / 24.3, FP32 12.2 / 17.9 / 13.1 / 16.0.
+constexpr int kAdj2OneRound = 256;  // compute units
+int adj2_waves(int strips2, int ny)
+{
+    for (int w : {10, 12, 14})
+        if (strips2 * ((ny + w - 7) / (w - 6)) <= kAdj2OneRound) return w;
+    return kAdj2Waves;
+}
+
+// Whether neighbouring tiles run on one XCD, whose L2 then serves the 6 rows and 6 columns they
+// share.  Measured, us per launch without / with: FP32 350 x 300 13.1 / 12.2, 512^2 18.2 / 17.3,
+// 700 x 650 30.5 / 30.0; FP64 256 x 200 15.5 / 15.1, 350 x 300 16.4 / 15.5, but 512^2, where its
+// workgroups run in two rounds, 28.2 / 29.6: FP64 in one round only.
+bool adj2_xcd(bool f32, int blocks2) { return f32 || blocks2 <= kAdj2OneRound; }
+
+// waves2: 0 = adj2_waves' choice
+AdjLayout adj_layout(const lbm_params& p, int ld, size_t pop_bytes, int K, int waves2 = 0)
 {
     AdjLayout L;
     L.tsz = p.prec == LBM_FP32_SHIFTED ? sizeof(float) : sizeof(double);
@@ -748,8 +779,9 @@ AdjLayout adj_layout(const lbm_params& p, int ld, size_t pop_bytes, int K)
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
     L.strips = (p.nx + kAdjW - 1) / kAdjW;
     L.blocks = L.strips * ((p.ny + kAdjRows - 1) / kAdjRows);
-    constexpr int R2 = Adj2Lds<kAdj2Waves>::R;
     L.strips2 = (p.nx + kAdj2W - 1) / kAdj2W;
+    L.waves2 = waves2 ? waves2 : adj2_waves(L.strips2, p.ny);
+    const int R2 = L.waves2 - 6;
     L.blocks2 = L.strips2 * ((p.ny + R2 - 1) / R2);
     L.nacc = (size_t)(L.blocks > L.blocks2 ? L.blocks : L.blocks2) * kAcc;
     size_t o = 0;
@@ -774,7 +806,8 @@ bool adj_launch(AdjArgs& A, const void* rec, const void* rec_lo, void* lam[2], i
     A.rec_lo = rec_lo;
     A.lam_in = lam[li];
     A.lam_out = lam[li ^ 1];
-    if (rec_lo) launch_adj2_step(f32, nt, L.blocks2, s, A);
+    if (rec_lo && f32) launch_adj2<float>(L.waves2, nt, L.blocks2, s, A);
+    else if (rec_lo) launch_adj2<double>(L.waves2, nt, L.blocks2, s, A);
     else launch_adj_step(f32, nt, L.blocks, s, A);
     li ^= 1;
     return hip_ok(hipGetLastError(), "adjoint step launch");
@@ -907,7 +940,9 @@ int lbm_adjoint_fields(lbm_ctx* c, const double* dL_drho_T, const double* dL_dux
     const int K = recorded ? 1 : c->ckpt_K;
     const int64_t S = recorded ? 1 : (T_end + K - 1) / K;
     if (!recorded && S > c->ckpt_slots) return LBM_ESTATE;
-    const AdjLayout L = adj_layout(P, c->ld, c->pop_bytes, K);
+    AdjLayout L = adj_layout(P, c->ld, c->pop_bytes, K);
+    // smaller tiles have more accumulators; a workspace without room for them takes the larger
+    if (adj_bytes < L.total) L = adj_layout(P, c->ld, c->pop_bytes, K, kAdj2Waves);
     if ((!recorded && rec_bytes < L.rec_bytes) || adj_bytes < L.total) {
         lbm_set_error("lbm_adjoint: record or adjoint workspace smaller than lbm_adjoint_layout requires");
         return LBM_EINVAL;
@@ -932,6 +967,7 @@ int lbm_adjoint_fields(lbm_ctx* c, const double* dL_drho_T, const double* dL_dux
     A.acc = acc;
     A.strips = L.strips;
     A.strips2 = L.strips2;
+    A.xcd = adj2_xcd(f32, L.blocks2);
     A.lplane = lp;
     const bool nt = 2 * 9 * lp * L.tsz <= kStreamBytes;  // streaming lambda stores on small lattices
     A.rplane = nn;
