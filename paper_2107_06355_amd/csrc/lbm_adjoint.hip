@@ -490,6 +490,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     __shared__ __align__(16) char ubuf[Adj2Lds<NW>::union_bytes(sizeof(T))];
     T(*lam)[NW][64] = reinterpret_cast<T(*)[NW][64]>(ubuf);
     double(*red)[R][64] = reinterpret_cast<double(*)[R][64]>(ubuf);
+    fetch_args<AdjArgs, NW - 1>();
     const StepArgs& S = A.S;
     const int lane = threadIdx.x & 63;
     const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -506,7 +507,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     const int yw = S.walls ? (y < 0 ? 0 : (y >= S.ny ? S.ny - 1 : y))
                            : (S.ny >= NW ? wrapx(y, S.ny) : ((y % S.ny) + S.ny) % S.ny);
     const bool own = k >= 3 && k < 3 + R && y < S.ny && lane >= 3 && lane < 3 + kAdj2W && xs < S.nx;
-    const double acc_prev = (k < kAcc && lane == kTotalLane) ? A.acc[(size_t)tile * kAcc + k] : 0.0;
+    // (through a vector register's address: a scalar load would be waited for before the others)
+    int vk = k;
+    asm("" : "+v"(vk));
+    const double acc_prev = (k < kAcc && lane == kTotalLane) ? A.acc[(size_t)tile * kAcc + vk] : 0.0;
     // what the first step leaves for the parameter sums of this node
     T a_psi = 0, a_dpsi = 0, a_dr = 0, a_vG = 0, a_sig = 0;
 

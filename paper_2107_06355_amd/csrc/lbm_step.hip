@@ -220,6 +220,7 @@ template <typename T, int MODE, bool WALLS, bool NT = false>
 __global__ __launch_bounds__(64 * k2WavesOf<T>) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : LBM_K2_EU_F64)))
 void k_step2_blk(StepArgs A)
 {
+    fetch_args<StepArgs, k2WavesOf<T> - 1>();
     __shared__ Step2Lds<T> S;
     const int nb = gridDim.x;
     const int logical = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);  // XCD-contiguous blocks
@@ -234,6 +235,7 @@ template <typename T, int MODE, bool WALLS, bool NT = false>
 __global__ __launch_bounds__(64 * k2rWavesOf<T>) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 4)))
 void k_step2_rows2(StepArgs A)
 {
+    if constexpr (NT) fetch_args<StepArgs, k2rWavesOf<T> - 1>();
     __shared__ Step2RowsLds<T, k2rWavesOf<T>, 2> S;
     const int nb = gridDim.x;
     const int logical = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);  // XCD-contiguous blocks
