@@ -42,6 +42,7 @@ namespace lbmk {
 // 6%; the finite-difference solver: 9%), slower at 168 MB (walled 2048 x 1024 FP32:
 // 23.6 -> 27.7 us/step) and beyond.
 constexpr size_t kStreamBytes = (size_t)64 << 20;
+constexpr size_t kMallBytes = (size_t)256 << 20;  // the memory-side cache (MALL)
 
 constexpr int kStripW = 62;   // interior columns per wave (lanes 0 and 63 are the psi halo)
 
@@ -263,8 +264,9 @@ struct Plane<float> {
 // small lattice is 6 us).  One wave of the workgroup does it, the last, whose row is in the halo
 // and has the least to do.  Measured, us per step without / with: 400^2 FP32 4.00 / 3.80, FP64
 // 4.86 / 4.71, 600 x 250 FP32 4.17 / 4.06, 512^2 FP32 4.40 / 4.41, 700 x 600 FP32 6.17 / 6.09; by
-// every wave 512^2 4.47; two transposed steps at 256 x 200 FP64 11.0 / 10.5 per launch.  Lattices
-// beyond the streaming size (NT false) do not gain: 8192^2 613 / 614, 6144^2 FP64 642 / 646.
+// every wave 512^2 4.47; two transposed steps at 256 x 200 FP64 11.0 / 10.5 per launch.  Beyond
+// the streaming size FP64 gains within kMallBytes (1024^2 19.5 / 19.1, 1300^2 28.6 / 27.9), FP32 not
+// (1600^2 24.6 / 24.7), and beyond that neither does: 8192^2 613 / 614, 6144^2 FP64 642 / 646.
 template <typename Args, int WAVE>
 __device__ __forceinline__ void fetch_args()
 {
@@ -1022,7 +1024,7 @@ struct Step2RowsLds {
 // tile grown by 3 (wave k holds rows k + j NW, j < RPW), in the same four phases and with the
 // same node arithmetic.  The rows of one wave are processed one after the other inside each
 // phase; their loads are issued together.
-template <typename T, int MODE, bool WALLS, bool NT, int NW, int RPW>
+template <typename T, int MODE, bool WALLS, bool NT, bool ALL, int NW, int RPW>
 __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, int band, Step2RowsLds<T, NW, RPW>& S)
 {
     constexpr int NR = NW * RPW;
@@ -1072,13 +1074,14 @@ __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, in
     //    base and shape: two scalar registers more spilled 4 (8192^2 FP32 567 -> 573 us/step;
     //    the one-row kernel has room for them and gains 1.3% at 512^2).
     if (threadIdx.x == 0) S.eos = A.eos;
-    // FP64 loads every row, one that is not needed (or is solid) from a row that is there: a
+    // With ALL every row loads, one that is not needed (or is solid) from a row that is there: a
     // wave's loads are then the same on every path, so its first row waits for its own loads
-    // only and its node_psi runs while the second row's arrive (700^2 11.8 -> 11.1, 1024^2
-    // 20.4 -> 19.4, 2048^2 81.5 -> 80.4 us/step; 6144^2, bound by HBM, unchanged).  FP32 keeps
-    // the guards: 1600^2 24.5 -> 23.8 without them, but 600 x 250, whose lower tiles have rows
-    // to spare, 4.18 -> 4.24 and 8192^2 612 -> 617.
-    constexpr bool kAllRows = sizeof(T) == 8;
+    // only and its node_psi runs while the second row's arrive.  FP64 always (700^2 11.8 -> 11.1,
+    // 1024^2 20.4 -> 19.4, 2048^2 81.5 -> 80.4 us/step; 6144^2, bound by HBM, unchanged).  FP32
+    // where both buffers lie in the memory-side cache but are not streamed (kMallBytes: 1600^2
+    // 24.5 -> 24.0, 1800 x 1700 28.0 -> 27.5, walled 2048 x 1024 22.3 -> 22.0, 1024^2 the same);
+    // elsewhere it keeps the guards: without them 600 x 250, whose lower tiles have
+    // rows to spare, 4.18 -> 4.24, and 8192^2 612 -> 617.
     Row<T> R[RPW];
     double dr[RPW];
     T ps[RPW];
@@ -1088,7 +1091,7 @@ __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, in
         dr[j] = 0.0;
         ps[j] = (T)0;
         const View<T> V = make_view<T>(A.src, A.plane);
-        if constexpr (kAllRows) {
+        if constexpr (ALL) {
             const int rl = dk_of(kk) > 3 ? y0 : (walls ? min(max(r, 0), A.ny - 1) : rw_of(r));
             pull<T>(V, A, L.x, L.xm, L.xp, rl, R[j].g0, R[j].g);
         } else if (dk_of(kk) <= 3 && dl <= 3 && fluid_of(r)) {

@@ -231,17 +231,18 @@ void k_step2_blk(StepArgs A)
 
 // The same with two rows per wave (step2_tile_rows; the shape two_step_shape picks): FP32 12
 // waves at two workgroups per CU (6 waves per SIMD), FP64 8 waves (4 per SIMD).
-template <typename T, int MODE, bool WALLS, bool NT = false>
+// MALL: both buffers within kMallBytes (and not streamed), MODE_STEP only.
+template <typename T, int MODE, bool WALLS, bool NT = false, bool MALL = false>
 __global__ __launch_bounds__(64 * k2rWavesOf<T>) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 4)))
 void k_step2_rows2(StepArgs A)
 {
-    if constexpr (NT) fetch_args<StepArgs, k2rWavesOf<T> - 1>();
+    if constexpr (NT || (MALL && sizeof(T) == 8)) fetch_args<StepArgs, k2rWavesOf<T> - 1>();
     __shared__ Step2RowsLds<T, k2rWavesOf<T>, 2> S;
     const int nb = gridDim.x;
     const int logical = (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3);  // XCD-contiguous blocks
     int strip, band;
     if (!two_step_tile(A, logical, strip, band)) return;  // whole workgroup leaves together
-    step2_tile_rows<T, MODE, WALLS, NT, k2rWavesOf<T>, 2>(A, strip, band, S);
+    step2_tile_rows<T, MODE, WALLS, NT, MALL || sizeof(T) == 8, k2rWavesOf<T>, 2>(A, strip, band, S);
 }
 
 // Short and small periodic lattices: nsteps steps per launch (strip_steps; the shape strip_plan
@@ -628,7 +629,7 @@ bool launch_step2(lbm_ctx* c, void* rec, hipStream_t s, bool reduce = false)
     A.rec_plane = (size_t)c->P.nx * c->P.ny;
     const dim3 g(c->grid2), b(64 * (c->rows2 ? k2rWavesOf<T> : k2WavesOf<T>));
     // streaming stores for small lattices (kStreamBytes)
-    const bool nt = 2 * c->pop_bytes <= kStreamBytes;
+    const bool nt = 2 * c->pop_bytes <= kStreamBytes, mall = 2 * c->pop_bytes <= kMallBytes;
     if (c->rows2) {
         if (c->P.walls) {
             if (rec && nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_RECORD, true, true>), g, b, 0, s, A);
@@ -636,6 +637,7 @@ bool launch_step2(lbm_ctx* c, void* rec, hipStream_t s, bool reduce = false)
             else if (reduce && nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP_REDUCE, true, true>), g, b, 0, s, A);
             else if (reduce) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP_REDUCE, true>), g, b, 0, s, A);
             else if (nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, true, true>), g, b, 0, s, A);
+            else if (mall) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, true, false, true>), g, b, 0, s, A);
             else hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, true>), g, b, 0, s, A);
         } else {
             if (rec && nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_RECORD, false, true>), g, b, 0, s, A);
@@ -643,6 +645,7 @@ bool launch_step2(lbm_ctx* c, void* rec, hipStream_t s, bool reduce = false)
             else if (reduce && nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP_REDUCE, false, true>), g, b, 0, s, A);
             else if (reduce) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP_REDUCE, false>), g, b, 0, s, A);
             else if (nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, false, true>), g, b, 0, s, A);
+            else if (mall) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, false, false, true>), g, b, 0, s, A);
             else hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, false>), g, b, 0, s, A);
         }
         return hip_ok(hipGetLastError(), "k_step2_rows2 launch");
