@@ -60,7 +60,8 @@ def _tile_rows(lbm, prec, tile_rows):
 def kernel_name(lbm, P, shape=None):
     """Name of the step kernel (as rocprofv3 prints it) that advances lattice P, and its steps per launch.
     shape: (tile rows, wavefronts) of the two-step tile a lattice runs (Lattice.tile_shape()); by default
-    the one lbm_describe reports for P."""
+    the one lbm_describe reports for P.  Two rows per wavefront on a lattice of 64 to 256 MiB (both
+    buffers) run the kernel's own instance for that range, k_step2_rows2_mall<T, WALLS>."""
     var, rows, waves = lbm.describe(P)
     if shape is not None and var == lbm.VARIANT_BLOCK2:
         rows, waves = shape

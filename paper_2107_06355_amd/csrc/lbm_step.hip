@@ -231,10 +231,8 @@ void k_step2_blk(StepArgs A)
 
 // The same with two rows per wave (step2_tile_rows; the shape two_step_shape picks): FP32 12
 // waves at two workgroups per CU (6 waves per SIMD), FP64 8 waves (4 per SIMD).
-// MALL: both buffers within kMallBytes (and not streamed), MODE_STEP only.
-template <typename T, int MODE, bool WALLS, bool NT = false, bool MALL = false>
-__global__ __launch_bounds__(64 * k2rWavesOf<T>) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 4)))
-void k_step2_rows2(StepArgs A)
+template <typename T, int MODE, bool WALLS, bool NT, bool MALL>
+__device__ __forceinline__ void step2_rows2(const StepArgs& A)
 {
     if constexpr (NT || (MALL && sizeof(T) == 8)) fetch_args<StepArgs, k2rWavesOf<T> - 1>();
     __shared__ Step2RowsLds<T, k2rWavesOf<T>, 2> S;
@@ -243,6 +241,20 @@ void k_step2_rows2(StepArgs A)
     int strip, band;
     if (!two_step_tile(A, logical, strip, band)) return;  // whole workgroup leaves together
     step2_tile_rows<T, MODE, WALLS, NT, MALL || sizeof(T) == 8, k2rWavesOf<T>, 2>(A, strip, band, S);
+}
+template <typename T, int MODE, bool WALLS, bool NT = false>
+__global__ __launch_bounds__(64 * k2rWavesOf<T>) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 4)))
+void k_step2_rows2(StepArgs A)
+{
+    step2_rows2<T, MODE, WALLS, NT, false>(A);
+}
+// the same where both buffers take more than kStreamBytes and at most kMallBytes (fetch_args and
+// step2_tile_rows' ALL say what is different there; plain steps only)
+template <typename T, bool WALLS>
+__global__ __launch_bounds__(64 * k2rWavesOf<T>) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 4)))
+void k_step2_rows2_mall(StepArgs A)
+{
+    step2_rows2<T, MODE_STEP, WALLS, false, true>(A);
 }
 
 // Short and small periodic lattices: nsteps steps per launch (strip_steps; the shape strip_plan
@@ -637,7 +649,7 @@ bool launch_step2(lbm_ctx* c, void* rec, hipStream_t s, bool reduce = false)
             else if (reduce && nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP_REDUCE, true, true>), g, b, 0, s, A);
             else if (reduce) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP_REDUCE, true>), g, b, 0, s, A);
             else if (nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, true, true>), g, b, 0, s, A);
-            else if (mall) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, true, false, true>), g, b, 0, s, A);
+            else if (mall) hipLaunchKernelGGL((k_step2_rows2_mall<T, true>), g, b, 0, s, A);
             else hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, true>), g, b, 0, s, A);
         } else {
             if (rec && nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_RECORD, false, true>), g, b, 0, s, A);
@@ -645,7 +657,7 @@ bool launch_step2(lbm_ctx* c, void* rec, hipStream_t s, bool reduce = false)
             else if (reduce && nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP_REDUCE, false, true>), g, b, 0, s, A);
             else if (reduce) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP_REDUCE, false>), g, b, 0, s, A);
             else if (nt) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, false, true>), g, b, 0, s, A);
-            else if (mall) hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, false, false, true>), g, b, 0, s, A);
+            else if (mall) hipLaunchKernelGGL((k_step2_rows2_mall<T, false>), g, b, 0, s, A);
             else hipLaunchKernelGGL((k_step2_rows2<T, MODE_STEP, false>), g, b, 0, s, A);
         }
         return hip_ok(hipGetLastError(), "k_step2_rows2 launch");
