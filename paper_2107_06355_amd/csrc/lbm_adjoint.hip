@@ -46,7 +46,9 @@ struct AdjArgs {
     double* acc;         // [blocks][kAcc] running sums
     int strips;          // column strips of kAdjW outputs
     int strips2;         // column strips of kAdj2W outputs (two steps per launch)
-    int xcd;             // the two-step tiles of one XCD are neighbours (adj2_xcd)
+    unsigned xcd;        // two-step tiles per XCD where the tiles of one are neighbours (adj2_xcd), else 0
+    // ceil(2^32 / strips2), so that tile / strips2 = umulhi(tile, magic2); 0 where that is not exact
+    unsigned magic2;
     size_t lplane, rplane;
     double c_e, c_q;     // 1/(tau_e - 1/2), 1/(tau_eps - 1/2) of Eq. LiFS
     double inv_G;
@@ -494,9 +496,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     const StepArgs& S = A.S;
     const int lane = threadIdx.x & 63;
     const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // the grid is padded to a multiple of 8; XCD-contiguous tiles where adj2_xcd says so
-    const int tile = A.xcd ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) : (int)blockIdx.x;
-    const int strip = tile % A.strips2, band = tile / A.strips2;
+    // the grid is padded to a multiple of 8; XCD-contiguous tiles where adj2_xcd says so.  No division
+    // and no read of the grid size before the first load (350 x 300: FP32 11.7 -> 11.5 us, FP64 14.8 -> 14.6)
+    const unsigned tile = A.xcd ? (blockIdx.x & 7) * A.xcd + (blockIdx.x >> 3) : blockIdx.x;
+    const int band = A.magic2 ? __umulhi(tile, A.magic2) : tile / (unsigned)A.strips2;
+    const int strip = tile - band * A.strips2;
     if (band * R >= S.ny) return;  // whole workgroup leaves together
     const int xs = strip * kAdj2W - 3 + lane;  // unwrapped column of this lane
     // xs lies in [-3, nx + 60] and y in [-3, ny + NW - 5]: one wrap each way on lattices at
@@ -971,7 +975,10 @@ int lbm_adjoint_fields(lbm_ctx* c, const double* dL_drho_T, const double* dL_dux
     A.acc = acc;
     A.strips = L.strips;
     A.strips2 = L.strips2;
-    A.xcd = adj2_xcd(f32, L.blocks2);
+    A.xcd = adj2_xcd(f32, L.blocks2) ? (L.blocks2 + 7) / 8 : 0;
+    // exact for tiles (the padding's included) below 2^32 / strips2
+    const unsigned long long tiles2 = (unsigned long long)L.blocks2 + 8, d2 = L.strips2;
+    A.magic2 = d2 > 1 && tiles2 * d2 < (1ull << 32) ? (unsigned)(((1ull << 32) + d2 - 1) / d2) : 0;
     A.lplane = lp;
     const bool nt = 2 * 9 * lp * L.tsz <= kStreamBytes;  // streaming lambda stores on small lattices
     A.rplane = nn;
