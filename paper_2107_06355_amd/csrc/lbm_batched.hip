@@ -168,7 +168,7 @@ void k_batch_step2(const BatchItem* items, const int* tile_off, int B, char* buf
 
 // Many steps of short or small periodic lattices (strip_steps): workgroup w takes strip w of
 // the table (lattice, first column).
-template <typename T, int CAP>
+template <typename T, int CAP, bool NT>
 __global__ __launch_bounds__(CAP)
 void k_batch_strip(const BatchItem* items, const int2* strips, char* buf0, char* buf1, int cur, int halo, int nsteps,
                    int step)
@@ -178,17 +178,22 @@ void k_batch_strip(const BatchItem* items, const int2* strips, char* buf0, char*
     const int x0 = __builtin_amdgcn_readfirstlane(strips[blockIdx.x].y);
     const StepArgs A = items[b].A;
     const size_t off = items[b].off_bytes;
-    strip_steps<T, CAP, false>(A, (cur ? buf1 : buf0) + off, (cur ? buf0 : buf1) + off, x0, items[b].cols, items[b].out,
+    strip_steps<T, CAP, false, NT>(A, (cur ? buf1 : buf0) + off, (cur ? buf0 : buf1) + off, x0, items[b].cols, items[b].out,
                                halo, nsteps, step, nullptr, S);
 }
 
 template <typename T>
 void launch_batch_strip(int threads, dim3 g, hipStream_t s, const BatchItem* it, const int2* strips, char* b0, char* b1,
-                        int cur, int halo, int nsteps, int step)
+                        int cur, int halo, int nsteps, int step, bool nt)
 {
     auto go = [&](auto cap) {
         constexpr int CAP = decltype(cap)::value;
-        hipLaunchKernelGGL((k_batch_strip<T, CAP>), g, dim3(threads), 0, s, it, strips, b0, b1, cur, halo, nsteps, step);
+        if (nt)
+            hipLaunchKernelGGL((k_batch_strip<T, CAP, true>), g, dim3(threads), 0, s, it, strips, b0, b1, cur, halo, nsteps,
+                               step);
+        else
+            hipLaunchKernelGGL((k_batch_strip<T, CAP, false>), g, dim3(threads), 0, s, it, strips, b0, b1, cur, halo, nsteps,
+                               step);
     };
     if (threads <= 256) go(std::integral_constant<int, 256>());
     else if (threads <= 512) go(std::integral_constant<int, 512>());
@@ -553,16 +558,17 @@ static int step_grouped(lbm_batch* c, int64_t nsteps, hipStream_t s)
 static int step_strips(lbm_batch* c, int64_t nsteps, hipStream_t s)
 {
     const int halo = strip_halo(c->L.strip.steps);
+    const bool nt = 2 * c->L.off[c->B] <= kStreamBytes;  // both buffers small, as for a single lattice
     while (nsteps > 0) {
         const int64_t launches = (nsteps + c->L.strip.steps - 1) / c->L.strip.steps;
         const int n = (int)((nsteps + launches - 1) / launches);
         const dim3 g((unsigned)c->L.strips.size());
         if (c->prec == LBM_FP32_SHIFTED)
             launch_batch_strip<float>(c->L.strip.threads, g, s, c->items, c->strips, c->buf[0], c->buf[1], c->cur, halo, n,
-                                      (int)c->step);
+                                      (int)c->step, nt);
         else
             launch_batch_strip<double>(c->L.strip.threads, g, s, c->items, c->strips, c->buf[0], c->buf[1], c->cur, halo, n,
-                                       (int)c->step);
+                                       (int)c->step, nt);
         if (!hip_ok(hipGetLastError(), "k_batch_strip launch")) return LBM_EHIP;
         c->cur ^= 1;
         c->step += n;

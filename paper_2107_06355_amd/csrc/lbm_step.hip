@@ -259,12 +259,12 @@ void k_step2_rows2_mall(StepArgs A)
 
 // Short and small periodic lattices: nsteps steps per launch (strip_steps; the shape strip_plan
 // picks).  One partial per workgroup when REDUCE.
-template <typename T, int CAP, bool REDUCE>
+template <typename T, int CAP, bool REDUCE, bool NT>
 __global__ __launch_bounds__(CAP)
 void k_strip(StepArgs A, int cols, int out, int halo, int nsteps)
 {
     __shared__ StripLds<T, CAP> S;
-    strip_steps<T, CAP, REDUCE>(A, A.src, A.dst, (int)blockIdx.x * out, cols, out, halo, nsteps, 0,
+    strip_steps<T, CAP, REDUCE, NT>(A, A.src, A.dst, (int)blockIdx.x * out, cols, out, halo, nsteps, 0,
                                 A.partials + 3 * (size_t)blockIdx.x, S);
 }
 
@@ -691,10 +691,13 @@ bool launch_strip(lbm_ctx* c, int n, bool reduce, hipStream_t s)
     const int t = c->strip.threads, cols = strip_cols(c->P, t), out = strip_out(c->P, t, c->strip.steps);
     const int halo = strip_halo(c->strip.steps);
     const dim3 g(strip_groups(c)), b(t);
+    const bool nt = 2 * c->pop_bytes <= kStreamBytes;
     auto go = [&](auto cap) {
         constexpr int CAP = decltype(cap)::value;
-        if (reduce) hipLaunchKernelGGL((k_strip<T, CAP, true>), g, b, 0, s, A, cols, out, halo, n);
-        else hipLaunchKernelGGL((k_strip<T, CAP, false>), g, b, 0, s, A, cols, out, halo, n);
+        if (reduce && nt) hipLaunchKernelGGL((k_strip<T, CAP, true, true>), g, b, 0, s, A, cols, out, halo, n);
+        else if (reduce) hipLaunchKernelGGL((k_strip<T, CAP, true, false>), g, b, 0, s, A, cols, out, halo, n);
+        else if (nt) hipLaunchKernelGGL((k_strip<T, CAP, false, true>), g, b, 0, s, A, cols, out, halo, n);
+        else hipLaunchKernelGGL((k_strip<T, CAP, false, false>), g, b, 0, s, A, cols, out, halo, n);
     };
     if (t <= 256) go(std::integral_constant<int, 256>());
     else if (t <= 512) go(std::integral_constant<int, 512>());

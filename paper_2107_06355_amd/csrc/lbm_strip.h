@@ -106,8 +106,11 @@ struct StripLds {
 // Advance columns x0 .. x0 + out - 1 (all rows) of lattice A by nsteps steps from src to dst,
 // holding `cols` of them (all, or halo more on each side, halo >= 2 nsteps - 1); `step` is
 // added to A.step for the number of the first step.  REDUCE: the last step leaves the FP64 mass and
-// momentum of these columns in partial[0..2].
-template <typename T, int CAP, bool REDUCE>
+// momentum of these columns in partial[0..2].  NT: streaming stores, for small lattices as in the
+// other kernels (kStreamBytes).  Streamed, a larger lattice is no longer in the memory-side cache for
+// the next launch: 65536 x 16, us for 100 steps (and for one), streamed / not, FP64 1833 / 1708 (47.1 /
+// 38.9), FP32 991 / 941 (32.3 / 24.7).
+template <typename T, int CAP, bool REDUCE, bool NT>
 __device__ __forceinline__ void strip_steps(const StepArgs& A, const void* src, void* dst, int x0, int cols, int out,
                                             int halo, int nsteps, int step, double* partial, StripLds<T, CAP>& S)
 {
@@ -164,9 +167,16 @@ __device__ __forceinline__ void strip_steps(const StepArgs& A, const void* src, 
                 acc = a;
                 const WView<T> D = make_wview<T>(dst, A.plane);
                 const uint32_t off = (uint32_t)y * (uint32_t)A.ld + (uint32_t)x;
+                if constexpr (NT) {
 #pragma unroll
-                for (int i = 1; i < 9; ++i) __builtin_nontemporal_store(o[i], (T*)(D.mv[i] + off * (uint32_t)sizeof(T)));
-                __builtin_nontemporal_store(o0, (double*)(D.rest + off * 8u));
+                    for (int i = 1; i < 9; ++i)
+                        __builtin_nontemporal_store(o[i], (T*)(D.mv[i] + off * (uint32_t)sizeof(T)));
+                    __builtin_nontemporal_store(o0, (double*)(D.rest + off * 8u));
+                } else {
+#pragma unroll
+                    for (int i = 1; i < 9; ++i) *(T*)(D.mv[i] + off * (uint32_t)sizeof(T)) = o[i];
+                    *(double*)(D.rest + off * 8u) = o0;
+                }
             }
             break;
         }
