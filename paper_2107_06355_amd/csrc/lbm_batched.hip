@@ -558,7 +558,12 @@ static int step_grouped(lbm_batch* c, int64_t nsteps, hipStream_t s)
 static int step_strips(lbm_batch* c, int64_t nsteps, hipStream_t s)
 {
     const int halo = strip_halo(c->L.strip.steps);
-    const bool nt = 2 * c->L.off[c->B] <= kStreamBytes;  // both buffers small, as for a single lattice
+    // streaming stores of small batches, as of a lattice, and of those beyond the memory-side cache: us
+    // for one step, streamed / not, 155 MiB (204 FP64 lattices of 122 to 488 x 16) 47.4 / 43.2, 256 MiB
+    // (328 FP32 of 246 to 984 x 16) 72.7 / 67.1, 272 MiB (319 FP64 of 341 to 1364 x 7) 69.7 / 71.5, 297 MiB
+    // (265 FP64 of 195 to 780 x 16) 83.7 / 89.5, 560 MiB (2000 FP64 of 100 x 16) 120 / 148
+    const size_t bytes = 2 * c->L.off[c->B];
+    const bool nt = bytes <= kStreamBytes || bytes > kMallBytes;
     while (nsteps > 0) {
         const int64_t launches = (nsteps + c->L.strip.steps - 1) / c->L.strip.steps;
         const int n = (int)((nsteps + launches - 1) / launches);
