@@ -38,7 +38,7 @@ struct BatchItem {
     StepArgs A;           // per-lattice arguments (src/dst filled in the kernel)
     size_t off_bytes;     // byte offset of the lattice in each population buffer
     long long cell_off;   // offset of the lattice in the packed scalar fields
-    int cols, out;        // columns a strip workgroup holds and advances (lbm_strip.h)
+    int cols;             // columns a strip workgroup holds (lbm_strip.h)
 };
 
 template <typename T, int MODE>
@@ -178,8 +178,9 @@ void k_batch_strip(const BatchItem* items, const int2* strips, char* buf0, char*
     const int x0 = __builtin_amdgcn_readfirstlane(strips[blockIdx.x].y);
     const StepArgs A = items[b].A;
     const size_t off = items[b].off_bytes;
-    strip_steps<T, CAP, false, NT>(A, (cur ? buf1 : buf0) + off, (cur ? buf0 : buf1) + off, x0, items[b].cols, items[b].out,
-                               halo, nsteps, step, nullptr, S);
+    const int cols = items[b].cols, out = cols == A.nx ? cols : cols - 2 * halo;
+    strip_steps<T, CAP, false, NT>(A, (cur ? buf1 : buf0) + off, (cur ? buf0 : buf1) + off, x0, cols, out, halo, nsteps,
+                                   step, nullptr, S);
 }
 
 template <typename T>
@@ -248,10 +249,17 @@ struct Layout {
     std::vector<int> item_off;      // [B+1] one-step grouped items (strips x rows) before each lattice
     std::vector<int> tile_off;      // [B+1] two-step grouped tiles before each lattice
     StripPlan strip;                // how the strip kernel runs these lattices (0 threads: it does not)
-    std::vector<int2> strips;       // its workgroups: lattice, first column
+    std::vector<int2> strips;       // its workgroups (lattice, first column): three lists, see strip_list
+    size_t strip_first[4];          // where each list begins in `strips`, and the end of the last
     int any_walls;
     size_t off_items, off_item_off, off_tile_off, off_strips, ws_bytes;
 };
+
+// The strips of a launch of one, of two and of more steps (up to the plan's): a list each, since
+// fewer steps use up fewer columns.  us with one list for all / with three: 16 FP64 lattices of 4096 x 16,
+// one step 42.0 / 35.2, two 56.2 / 45.2; 60 FP64 lattices of 100 to 2000 x 1 to 16, one step 20.2 / 16.9
+int strip_list(int n) { return n > 2 ? 2 : n - 1; }
+int strip_list_steps(const StripPlan& s, int list) { return list == 2 || list + 1 > s.steps ? s.steps : list + 1; }
 
 int batch_layout(int B, const lbm_params* p, Layout& L)
 {
@@ -294,10 +302,13 @@ int batch_layout(int B, const lbm_params* p, Layout& L)
         L.any_walls |= p[b].walls != 0;
     }
     L.strip = strip_plan(B, p);
-    if (L.strip.threads)
-        for (int b = 0; b < B; ++b)
-            for (int x = 0, out = strip_out(p[b], L.strip.threads, L.strip.steps); x < p[b].nx; x += out)
+    for (int k = 0; k < 3; ++k) {
+        L.strip_first[k] = L.strips.size();
+        for (int b = 0; b < B && L.strip.threads; ++b)
+            for (int x = 0, out = strip_out(p[b], L.strip.threads, strip_list_steps(L.strip, k)); x < p[b].nx; x += out)
                 L.strips.push_back(int2{b, x});
+    }
+    L.strip_first[3] = L.strips.size();
     // workspace: per-lattice error words, the item records, the grouped-step item offsets
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
     L.off_items = al((size_t)B * 2 * sizeof(unsigned));
@@ -428,7 +439,6 @@ int lbm_init_batched(lbm_batch** out, int B, const lbm_params* p, void* f_a, voi
         host[b].off_bytes = L.off[b];
         host[b].cell_off = L.cells[b];
         host[b].cols = L.strip.threads ? strip_cols(P, L.strip.threads) : 0;
-        host[b].out = L.strip.threads ? strip_out(P, L.strip.threads, L.strip.steps) : 0;
         err0[2 * b] = 0u;
         err0[2 * b + 1] = 0xffffffffu;
     }
@@ -557,7 +567,6 @@ static int step_grouped(lbm_batch* c, int64_t nsteps, hipStream_t s)
 // strip kernel: launches of up to L.strip.steps steps, as equal as they come
 static int step_strips(lbm_batch* c, int64_t nsteps, hipStream_t s)
 {
-    const int halo = strip_halo(c->L.strip.steps);
     // streaming stores of small batches, as of a lattice, and of those beyond the memory-side cache: us
     // for one step, streamed / not, 155 MiB (204 FP64 lattices of 122 to 488 x 16) 47.4 / 43.2, 256 MiB
     // (328 FP32 of 246 to 984 x 16) 72.7 / 67.1, 272 MiB (319 FP64 of 341 to 1364 x 7) 69.7 / 71.5, 297 MiB
@@ -567,12 +576,14 @@ static int step_strips(lbm_batch* c, int64_t nsteps, hipStream_t s)
     while (nsteps > 0) {
         const int64_t launches = (nsteps + c->L.strip.steps - 1) / c->L.strip.steps;
         const int n = (int)((nsteps + launches - 1) / launches);
-        const dim3 g((unsigned)c->L.strips.size());
+        const int list = strip_list(n), halo = strip_halo(strip_list_steps(c->L.strip, list));
+        const dim3 g((unsigned)(c->L.strip_first[list + 1] - c->L.strip_first[list]));
+        const int2* strips = c->strips + c->L.strip_first[list];
         if (c->prec == LBM_FP32_SHIFTED)
-            launch_batch_strip<float>(c->L.strip.threads, g, s, c->items, c->strips, c->buf[0], c->buf[1], c->cur, halo, n,
+            launch_batch_strip<float>(c->L.strip.threads, g, s, c->items, strips, c->buf[0], c->buf[1], c->cur, halo, n,
                                       (int)c->step, nt);
         else
-            launch_batch_strip<double>(c->L.strip.threads, g, s, c->items, c->strips, c->buf[0], c->buf[1], c->cur, halo, n,
+            launch_batch_strip<double>(c->L.strip.threads, g, s, c->items, strips, c->buf[0], c->buf[1], c->cur, halo, n,
                                        (int)c->step, nt);
         if (!hip_ok(hipGetLastError(), "k_batch_strip launch")) return LBM_EHIP;
         c->cur ^= 1;

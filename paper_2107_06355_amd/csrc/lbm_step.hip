@@ -621,10 +621,10 @@ bool launch_record_step(lbm_ctx* c, void* rec, hipStream_t s)
     return hip_ok(hipGetLastError(), "k_step_blk(record) launch");
 }
 
-// workgroups of a strip launch (and partials of a reducing one)
-int strip_groups(const lbm_ctx* c)
+// workgroups of a strip launch of n steps (and partials of a reducing one)
+int strip_groups(const lbm_ctx* c, int n)
 {
-    const int out = strip_out(c->P, c->strip.threads, c->strip.steps);
+    const int out = strip_out(c->P, c->strip.threads, n);
     return (c->P.nx + out - 1) / out;
 }
 
@@ -688,9 +688,8 @@ bool launch_strip(lbm_ctx* c, int n, bool reduce, hipStream_t s)
     A.src = c->buf[c->cur];
     A.dst = c->buf[c->cur ^ 1];
     A.step = c->step;
-    const int t = c->strip.threads, cols = strip_cols(c->P, t), out = strip_out(c->P, t, c->strip.steps);
-    const int halo = strip_halo(c->strip.steps);
-    const dim3 g(strip_groups(c)), b(t);
+    const int t = c->strip.threads, cols = strip_cols(c->P, t), out = strip_out(c->P, t, n), halo = strip_halo(n);
+    const dim3 g(strip_groups(c, n)), b(t);
     const bool nt = 2 * c->pop_bytes <= kStreamBytes;
     auto go = [&](auto cap) {
         constexpr int CAP = decltype(cap)::value;
@@ -1109,18 +1108,18 @@ int lbm_step(lbm_ctx* c, int64_t nsteps, void* stream)
                         "checkpoint copy"))
                 return LBM_EHIP;
         }
-        // (adjoint forwards, which record or checkpoint, take the steps that their recomputation takes)
-        if (c->strip.threads && !c->rec_all && c->ckpt_K == 0) {
-            // up to the next reducing step, in launches of equal length
-            const int64_t to_red = re > 0 ? (re - c->step % re) % re + 1 : nsteps;
-            const int64_t todo = to_red < nsteps - k ? to_red : nsteps - k;
+        // strips: the steps up to the next reducing one, in launches of equal length (adjoint
+        // forwards, which record or checkpoint, take the steps that their recomputation takes)
+        const int64_t to_red = re > 0 ? (re - c->step % re) % re + 1 : nsteps;
+        const int64_t todo = to_red < nsteps - k ? to_red : nsteps - k;
+        if (c->strip.threads && !c->rec_all && c->ckpt_K == 0 && strip_runs(c->P, todo)) {
             const int64_t launches = (todo + c->strip.steps - 1) / c->strip.steps;
             const int n = (int)((todo + launches - 1) / launches);
             const bool last = re > 0 && (c->step + n - 1) % re == 0;
             if (!(f32 ? launch_strip<float>(c, n, last, s) : launch_strip<double>(c, n, last, s))) return LBM_EHIP;
             if (last) {
                 double* row = c->hist + 4 * (c->hist_count % kHistCap);
-                if (!launch_reduce_n(c, strip_groups(c), row, (long long)c->step + n - 1, 1, s)) return LBM_EHIP;
+                if (!launch_reduce_n(c, strip_groups(c, n), row, (long long)c->step + n - 1, 1, s)) return LBM_EHIP;
                 c->hist_count++;
             }
             c->cur ^= 1;

@@ -29,7 +29,8 @@ struct StripPlan {
     int threads, steps;
 };
 inline int strip_halo(int steps) { return 2 * steps - 1; }
-// columns that a workgroup holds of lattice p (its width: resident), and those it advances
+// columns that a workgroup holds of lattice p (its width: resident), and those it advances in a
+// launch of `steps` steps
 inline int strip_cols(const lbm_params& p, int threads)
 {
     const int c = threads / p.ny;
@@ -94,6 +95,16 @@ inline StripPlan strip_plan(int B, const lbm_params* p)
     }
     return best;
 }
+
+// Whether a single lattice leaves a launch of `steps` steps to the strip kernel.  One and two steps
+// run on the one- and two-step kernels, whose smaller workgroups take less time for so little work,
+// except on wide lattices of so few rows that tiles of 10 and more are mostly empty and yet more
+// than the chip has compute units.  Measured, us per call, strips / those kernels: one step 1024 x 1
+// FP64 5.05 / 3.73, 2048 x 4 FP64 4.58 / 4.09, 1500 x 3 FP32 4.16 / 3.85, 4096 x 16 FP32 5.06 / 4.52,
+// but 16384 x 4 FP64 5.1 / 5.7, 65536 x 1 FP32 4.3 / 6.4; two steps 1024 x 1 FP64 6.8 / 5.5, 700 x 12
+// FP32 6.0 / 5.6, but 16384 x 4 FP64 6.6 / 8.4, 65536 x 1 FP32 5.6 / 10.7; three steps, where the other
+// kernels take two launches, 1024 x 1 FP64 8.5 / 10.0, 4096 x 16 FP32 8.5 / 11.4.
+inline bool strip_runs(const lbm_params& p, long long steps) { return steps > 2 || (p.ny <= 4 && p.nx >= 15000); }
 
 template <typename T, int CAP>
 struct StripLds {
