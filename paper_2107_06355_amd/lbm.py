@@ -440,10 +440,10 @@ class Batch:
         _check(load().lbm_macros_batched(self._h, rho.data_ptr(), ux.data_ptr(), uy.data_ptr(),
                                          C.c_void_p(self.stream.cuda_stream)), "lbm_macros_batched")
         out = []
-        # one copy saves 20 us twice; a large one is memory mapped anew (and faulted in) on every call,
-        # which fields of a third of its size are not: 107 lattices of 947 x 24 20.5 ms in three
-        # copies, 31.0 in one
-        one = fields.numel() * 8 <= 8 << 20
+        # one copy saves two calls of about 20 us, but a larger one is slower by more: the host pages of a
+        # new allocation beyond some size are mapped anew on every call.  us, one copy / three: 128 KiB
+        # 17 / 38, 1000 KiB 56 / 78, 2000 KiB 112 / 118, 2400 KiB 143 / 139, 3000 KiB 674 / 172, 64 MB 16000 / 3800
+        one = fields.numel() * 8 <= 2 << 20
         r, u, v = fields.cpu().numpy() if one else (f.cpu().numpy() for f in fields)
         for b, (ny, nx) in enumerate(self.shapes):
             sl = slice(self.offsets[b], self.offsets[b + 1])
