@@ -56,7 +56,10 @@ constexpr int kStripW = 62;   // interior columns per wave (lanes 0 and 63 are t
 // 512^2 FP32 4.54 -> 4.43 (its shaped loop is FP64), 600 x 250 with walls and tau(rho) FP32 4.57 ->
 // 4.44, 2048 x 1024 FP64 46.3 -> 45.6, 200 x 2 FP64 1.15 -> 1.07; the adjoint's dp/drho: two transposed steps at 512^2 FP32
 // 17.4 -> 16.7, 256 x 200 FP64 11.3 -> 11.1; every population and gradient bit-identical.
-// A zero, infinite or NaN argument gives NaN (sqrt: for 0 too; the callers select).
+// A divisor of zero or infinity gives NaN, so dev_eos_p has an instance with IEEE divisions for the
+// pressure that lbm_macros returns, infinite at a pole of the base EOS (psi is zero and the node flagged
+// there either way).  fast_sqrt(0) is 0 (the end of an ellipse), fast_sqrt_pos(0) NaN: psi's callers
+// ask for psi^2 > 0 first.
 __device__ __forceinline__ double fast_rcp(double d)
 {
     double r = __builtin_amdgcn_rcp(d);
@@ -68,15 +71,22 @@ __device__ __forceinline__ double fast_div(double n, double d)
     const double r = fast_rcp(d), q = n * r;
     return fma(fma(-d, q, n), r, q);
 }
-__device__ __forceinline__ double fast_sqrt(double a)
+// sqrt(a) from y, the estimate of 1/sqrt(a)
+__device__ __forceinline__ double sqrt_refined(double a, double y)
 {
-    const double y = __builtin_amdgcn_rsq(a);
     double g = a * y, h = 0.5 * y;
     const double e = fma(-h, g, 0.5);
     g = fma(g, e, g);
     h = fma(h, e, h);
     g = fma(fma(-g, g, a), h, g);
     return fma(fma(-g, g, a), h, g);
+}
+__device__ __forceinline__ double fast_sqrt_pos(double a) { return sqrt_refined(a, __builtin_amdgcn_rsq(a)); }
+__device__ __forceinline__ double fast_sqrt(double a)
+{
+    // the estimate for 0, infinity, becomes 0: its low word is 0 already
+    const double y = __builtin_amdgcn_rsq(a);
+    return sqrt_refined(a, __hiloint2double(a == 0.0 ? 0 : __double2hiint(y), __double2loint(y)));
 }
 
 // ----------------------------------------------------------------- device EOS
@@ -90,21 +100,24 @@ struct DevEos {
 
 // base, shape: E's own, apart from the record so that a caller whose record lies in LDS can give
 // them from scalar registers (a scalar branch instead of a lane mask that waits for an LDS read)
+template <bool IEEE>
 __device__ __forceinline__ double dev_base_p(const DevEos& E, int base, double r)
 {
+    auto div = [](double n, double d) { return IEEE ? n / d : fast_div(n, d); };
     if (base == LBM_BASE_CS) {
         const double n = 0.25 * E.b * r, m = 1.0 - n;
-        return E.scale * (fast_div(E.RT * r * (1.0 + n * (1.0 + n * (1.0 - n))), m * m * m) - E.aal * r * r);
+        return E.scale * (div(E.RT * r * (1.0 + n * (1.0 + n * (1.0 - n))), m * m * m) - E.aal * r * r);
     }
     const double br = E.b * r;
-    return E.scale * (fast_div(E.RT * r, 1.0 - br) - fast_div(E.aal * r * r, 1.0 + br * (2.0 - br)));
+    return E.scale * (div(E.RT * r, 1.0 - br) - div(E.aal * r * r, 1.0 + br * (2.0 - br)));
 }
 
+template <bool IEEE = false>
 __device__ __forceinline__ double dev_eos_p(const DevEos& E, int base, int shape, double r)
 {
-    if (shape == LBM_SHAPE_NONE) return dev_base_p(E, base, r);
-    if (r <= E.rho_v) return E.k_vap * dev_base_p(E, base, r);
-    if (r >= E.rho_l) return dev_base_p(E, base, r) + E.dP;
+    if (shape == LBM_SHAPE_NONE) return dev_base_p<IEEE>(E, base, r);
+    if (r <= E.rho_v) return E.k_vap * dev_base_p<IEEE>(E, base, r);
+    if (r >= E.rho_l) return dev_base_p<IEEE>(E, base, r) + E.dP;
     if (shape == LBM_SHAPE_PENG) return E.p0 + E.theta * (r - E.rho_v) * (r - E.rho_l) * (r - E.rho_m);
     if (r <= E.rho_max) {
         const double d = r - E.rho_max;
@@ -414,7 +427,7 @@ __device__ __forceinline__ T node_psi(const StepArgs& A, const DevEos& E, int ba
     const double q = (p - rho * (1.0 / 3.0)) * A.cd.two_inv_G;
     if (check && !(q >= 0.0 && rho > 0.0)) flag_unstable(A, dstep);
     if (sizeof(T) == 4) return (T)(q > 0.0 ? __builtin_amdgcn_sqrtf((float)q) : 0.0f);
-    return (T)(q > 0.0 ? fast_sqrt(q) : 0.0);
+    return (T)(q > 0.0 ? fast_sqrt_pos(q) : 0.0);
 }
 template <typename T>
 __device__ __forceinline__ T node_psi(const StepArgs& A, double drho, bool check, int dstep = 0)
@@ -522,7 +535,7 @@ __device__ __forceinline__ bool node_collide(const StepArgs& A, const Lane& L, i
         if (A.o_ux) A.o_ux[o] = (double)ux;
         if (A.o_uy) A.o_uy[o] = (double)uy;
         if (A.o_psi) A.o_psi[o] = (double)psB;
-        if (A.o_p) A.o_p[o] = dev_eos_p(A.eos, rho_d);
+        if (A.o_p) A.o_p[o] = dev_eos_p<true>(A.eos, A.eos.base, A.eos.shape, rho_d);
         if (A.o_fx) A.o_fx[o] = (double)Fx;
         if (A.o_fy) A.o_fy[o] = (double)Fy;
     }

@@ -240,7 +240,7 @@ void k_fd_step(FdArgs args, const double* rho, const double* u, const double* v,
         aU[q] = fu[k];
         aV[q] = fv[k];
         aP[q] = pe;
-        aS[q] = qq > 0.0 ? fast_sqrt(qq) : 0.0;
+        aS[q] = qq > 0.0 ? fast_sqrt_pos(qq) : 0.0;
     }
     __syncthreads();
     if (A.walls) {
@@ -261,7 +261,7 @@ void k_fd_step(FdArgs args, const double* rho, const double* u, const double* v,
         const double pe = dev_eos_p(A.eos, nr);
         const double qq = (pe - nr * (1.0 / 3.0)) * A.two_inv_G;
         bP[tid] = pe;
-        bS[tid] = qq > 0.0 ? fast_sqrt(qq) : 0.0;
+        bS[tid] = qq > 0.0 ? fast_sqrt_pos(qq) : 0.0;
     }
     __syncthreads();
     if (A.walls) {
