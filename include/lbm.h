@@ -138,7 +138,8 @@ typedef struct {
     lbm_eos eos;         /* built by lbm_eos_build */
     int tile_rows;       /* LBM_VARIANT_BLOCK2 tile height: 0 = the library's choice (below);
                           * -1 = the fastest candidate, timed on the device by lbm_init
-                          * (FP32: one-row tiles and two-row heights 14..18; FP64: 7..10);
+                          * (FP32: one-row tiles and two-row heights 14..18; FP64: 7..10;
+                          * and the height 0 would run);
                           * > 0 = that height (FP32: 10 = one row per wavefront, 11..18 =
                           * two rows; FP64: 5..10).  Populations do not depend on it beyond
                           * the compiler's FMA contraction between the one- and two-row

@@ -739,9 +739,9 @@ inline bool tile_rows_valid(const lbm_params& p)
     const int lo = f32 ? k2WavesOf<float> - 6 : k2rRowsOf<double> / 2, hi = f32 ? k2rRowsOf<float> : k2rRowsOf<double>;
     return p.tile_rows >= lo && p.tile_rows <= hi;
 }
-// The library's choice (tile_rows 0, and the shape before timing for -1): FP64 two-row tiles
-// of 10 rows; FP32 one-row tiles of 10 rows, or two-row tiles of 18 on lattices of at least
-// kRows2MinTiles of them (measured: see k2rWavesOf).
+// The fixed rule (what lbm_describe reports for tile_rows 0 and -1; run_shape starts from it): FP64
+// two-row tiles of 10 rows; FP32 one-row tiles of 10 rows, or two-row tiles of 18 on lattices of at
+// least kRows2MinTiles of them (measured: see k2rWavesOf).
 inline TwoStepShape two_step_shape(const lbm_params& p)
 {
     const bool f32 = p.prec == LBM_FP32_SHIFTED;
@@ -800,12 +800,13 @@ inline TwoStepShape run_shape(const lbm_params& p)
 // 47.6 us per launch with 16-row tiles against 49.7 with 18 and 51.2 with one-row tiles;
 // 4096 x 2048 184.5 us with 17 rows against 201.7 with 18 and 213.7 with 16; 8192^2 best with
 // 18).  Lattices the chip runs in one round keep the library's choice.
+// (Any other tile_rows: the fixed rule's or the named height alone, which sizes the workspace.)
 constexpr int kMaxShapes = 8;
 inline int two_step_candidates(const lbm_params& p, TwoStepShape out[kMaxShapes])
 {
     const bool f32 = p.prec == LBM_FP32_SHIFTED;
     int n = 0;
-    out[n++] = two_step_shape(p);
+    out[n++] = p.tile_rows == -1 ? run_shape(p) : two_step_shape(p);
     if (p.tile_rows != -1) return n;
     const long long strips = (p.nx + k2Cols - 1) / k2Cols;
     const int hmax = f32 ? k2rRowsOf<float> : k2rRowsOf<double>;

@@ -229,7 +229,7 @@ void k_step2_blk(StepArgs A)
     step2_tile<T, MODE, WALLS, NT>(A, strip, band, S);
 }
 
-// The same with two rows per wave (step2_tile_rows; the shape two_step_shape picks): FP32 12
+// The same with two rows per wave (step2_tile_rows; run_shape says where): FP32 12
 // waves at two workgroups per CU (6 waves per SIMD), FP64 8 waves (4 per SIMD).
 template <typename T, int MODE, bool WALLS, bool NT, bool MALL>
 __device__ __forceinline__ void step2_rows2(const StepArgs& A)

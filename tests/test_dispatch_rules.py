@@ -1,5 +1,6 @@
 """The dispatch rules of the library's headers (host code), compiled into a small program and called on
-sizes: which launches the strip kernel takes and how much of its work is recomputed columns."""
+sizes: which launches the strip kernel takes, how much of its work is recomputed columns, and which
+two-step tiles are timed."""
 import os
 import shutil
 import subprocess
@@ -16,7 +17,8 @@ PROGRAM = r"""
 #include "lbm_device.h"
 #include "lbm_strip.h"
 using namespace lbmk;
-// one line in: precision, steps, lattices, then nx ny of each
+// one line in: precision, steps, lattices, then nx ny of each; steps 0: the two-step tiles of the first
+// lattice, rows and waves of the library's pick and then of every timed candidate
 int main()
 {
     int prec, steps, n;
@@ -26,6 +28,16 @@ int main()
             q = lbm_params();
             q.prec = prec;
             if (std::scanf("%d %d", &q.nx, &q.ny) != 2) return 1;
+        }
+        if (steps == 0) {
+            const TwoStepShape pick = run_shape(p[0]);
+            std::printf("%d %d", pick.rows, pick.waves);
+            p[0].tile_rows = -1;
+            TwoStepShape c[kMaxShapes];
+            const int k = two_step_candidates(p[0], c);
+            for (int i = 0; i < k; ++i) std::printf(" %d %d", c[i].rows, c[i].waves);
+            std::printf("\n");
+            continue;
         }
         const StripPlan s = strip_plan(n, p.data());
         std::printf("%d %d %d", s.threads, s.steps, (int)strip_runs(p[0], steps));
@@ -78,3 +90,18 @@ def test_strips_recompute_only_the_columns_a_launch_uses_up(rules, prec):
         for n in range(1, steps + 1):
             cols, out = rules([(prec, n, 1, nx, ny)])[0][3:]
             assert cols == threads // ny and out == cols - 2 * (2 * n - 1), (nx, ny, n)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_timed_tiles_include_the_one_that_runs_untimed(rules, prec):
+    """tile_rows = -1 times, among others, the height that tile_rows = 0 runs; each shape once."""
+    sizes = [(1400, 225), (384, 785), (100, 2580)] if prec == 0 else [(249, 2196), (211, 2695)]
+    sizes += [(nx, ny) for nx in range(60, 2500, 83) for ny in range(60, 2500, 97)]
+    picks = set()
+    for (nx, ny), got in zip(sizes, rules([(prec, 0, 1, nx, ny) for nx, ny in sizes])):
+        pick, cand = tuple(got[:2]), list(zip(got[2::2], got[3::2]))
+        assert pick in cand and len(set(cand)) == len(cand) <= 8, (nx, ny, got)
+        if len(cand) > 1:
+            picks.add(pick[0])
+            assert set(range(7, 11) if prec == 0 else [10] + list(range(14, 19))) <= {r for r, _ in cand}, (nx, ny, got)
+    assert picks & ({5, 6} if prec == 0 else {12})  # heights outside the timed range were among them
