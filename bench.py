@@ -41,6 +41,7 @@ METRIC = "MLUPS + HBM GB/s (%roofline), FP32-shifted vs FP64 D2Q9; adjoint/fwd t
 # algorithmic bytes per cell update: 8 moving populations read + written, rest population FP64 read + written
 BYTES = {"fp32": 8 * 4 * 2 + 8 * 2, "fp64": 9 * 8 * 2}
 STREAM_BYTES = 64 << 20  # the library streams its stores when both population buffers take at most this
+MALL_BYTES = 256 << 20  # the memory-side cache: two-row tiles have an instance of their own up to this
 LEGS = ("c3", "c2", "parity", "sweep", "aa", "batched", "fd", "adjoint", "cpu")
 
 
@@ -58,10 +59,10 @@ def _tile_rows(lbm, prec, tile_rows):
 
 
 def kernel_name(lbm, P, shape=None):
-    """Name of the step kernel (as rocprofv3 prints it) that advances lattice P, and its steps per launch.
+    """Name of the step kernel of P's variant, tile, walls and stores, and its steps per launch: the
+    general instance, which launched_kernel replaces where the library has one for the lattice's size.
     shape: (tile rows, wavefronts) of the two-step tile a lattice runs (Lattice.tile_shape()); by default
-    the one lbm_describe reports for P.  Two rows per wavefront on a lattice of 64 to 256 MiB (both
-    buffers) run the kernel's own instance for that range, k_step2_rows2_mall<T, WALLS>."""
+    the one lbm_describe reports for P."""
     var, rows, waves = lbm.describe(P)
     if shape is not None and var == lbm.VARIANT_BLOCK2:
         rows, waves = shape
@@ -76,6 +77,22 @@ def kernel_name(lbm, P, shape=None):
     # one row per wavefront: tiles of waves - 6 rows; two: up to 2 waves - 6
     kern = "k_step2_rows2" if rows > waves - 6 else "k_step2_blk"
     return "%s<%s, 0, %s, %s>" % (kern, t, "true" if P.walls else "false", "true" if nt else "false"), 2
+
+
+def launched_kernel(lbm, P, shape=None):
+    """Name of the kernel (as rocprofv3 prints it) that runs plain steps of lattice P, and its (most) steps
+    per launch: kernel_name's, but the strip kernel where lbm_describe_strip names one, and the instance
+    of the two-row tiles for lattices of 64 to 256 MiB (both buffers)."""
+    t = "float" if P.prec == lbm.FP32_SHIFTED else "double"
+    both = 2 * lbm.layout(P)[1]
+    threads, steps = lbm.describe_strip(P)
+    if threads:
+        cap = next(c for c in (256, 512, 1024) if threads <= c)
+        return "k_strip<%s, %d, false, %s>" % (t, cap, "true" if both <= STREAM_BYTES else "false"), steps
+    name, n = kernel_name(lbm, P, shape)
+    if name.startswith("k_step2_rows2<") and STREAM_BYTES < both <= MALL_BYTES:
+        name = "k_step2_rows2_mall<%s, %s>" % (t, "true" if P.walls else "false")
+    return name, n
 
 
 # ---------------------------------------------------------------------------
@@ -204,7 +221,7 @@ def workload_leg(lbm, make, prec, steps, warmup, kernel_steps):
     del L
     # the step kernel alone, in the tile shape the window ran
     L, e = make(prec, 0, shape[0] if shape else 0)
-    kname, spl = kernel_name(lbm, L.P, shape)
+    kname, spl = launched_kernel(lbm, L.P, shape)
     ksteps = max(spl, kernel_steps - kernel_steps % spl)
     ksec, _ = time_steps(L, ksteps, 20)
     L.check()
@@ -370,7 +387,7 @@ def sweep_leg(lbm, sides, steps, only=""):
                 continue
             L, e = droplet_lattice(lbm, side, prec, 0)
             tiles = tiles_of(lbm, L)
-            kname, spl = kernel_name(lbm, L.P, L.tile_shape() if tiles else None)
+            kname, spl = launched_kernel(lbm, L.P, L.tile_shape() if tiles else None)
             n = max(spl, steps - steps % spl)
             sec, _ = time_steps(L, n, 20)
             L.check()

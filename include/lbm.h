@@ -60,11 +60,11 @@ typedef enum { LBM_FP64 = 0, LBM_FP32_SHIFTED = 1 } lbm_prec;
  * workgroup advances a tile 58 columns wide by two time steps per launch and
  * keeps the intermediate populations in LDS (temporal blocking; a reducing
  * step ends a launch, and checkpoint boundaries and odd counts run single
- * steps on BLOCK).  AUTO runs periodic lattices of at most 16 rows or 1024
- * nodes (recording and checkpointing off, tile_rows = 0) up to 16 steps per
- * launch, or any number, with the populations in LDS.  The tile: FP64, 8 wavefronts of two rows each, 10 rows;
- * FP32, 16 wavefronts of one row, 10 rows, or on lattices of at least 4096
- * such tiles 12 wavefronts of two rows, 18 rows.  AUTO is BLOCK2.
+ * steps on BLOCK).  The tile: FP64, 8 wavefronts of two rows each, 5 to 10
+ * rows; FP32, 16 wavefronts of one row, 10 rows, or 12 wavefronts of two rows,
+ * 11 to 18 rows (lbm_params.tile_rows).  AUTO is BLOCK2, but runs periodic
+ * lattices of at most 16 rows or 1024 nodes on strips that keep the
+ * populations in LDS for many steps (lbm_describe_strip).
  * AA: one population buffer updated in place with the AA access pattern
  * (even steps read and write each node's own slots, odd steps read from and
  * write to the neighbours, bounce-back included), for lattices whose second
@@ -165,6 +165,15 @@ int lbm_layout(const lbm_params* p, int* ld_out, size_t* pop_bytes_out, size_t* 
  * 4 wavefronts per workgroup. */
 int lbm_describe(const lbm_params* p, int* variant_out, int* band_rows_out, int* waves_out);
 
+/* The strip kernel that AUTO with tile_rows = 0 runs on periodic lattices of
+ * at most 16 rows or 1024 nodes: threads per workgroup (one node each) and the
+ * most steps per launch, or 0 and 0 for a lattice that does not run it.  A
+ * lattice that runs it still takes steps that record or checkpoint on BLOCK2's
+ * kernels, and so one or two steps at a time (to the end of an lbm_step or to a
+ * reduction), unless it has at most 4 rows and at least 15000 columns.
+ * Batches run it by lbm_step_batched's rule. */
+int lbm_describe_strip(const lbm_params* p, int* threads_out, int* steps_out);
+
 /* Create a context over caller buffers f_a, f_b (lbm_layout bytes each) and
  * workspace ws, and write the initial state f_i(0) = f^eq_i(rho0, u0)
  * (Sec. III.A) into f_a; in LBM_FP32_SHIFTED the FP64 rest population takes
@@ -195,7 +204,8 @@ int lbm_init(lbm_ctx** ctx, const lbm_params* p, void* f_a, void* f_b, void* ws,
 int lbm_init_static(lbm_ctx** ctx, const lbm_params* p, void* f_a, void* f_b, const double* rho0,
                     const double* ux0, const double* uy0, void* stream);
 
-/* The two-step tile a context runs (LBM_VARIANT_BLOCK2): output rows and
+/* The two-step tile a context runs (LBM_VARIANT_BLOCK2; where it runs two steps
+ * at a time, if lbm_describe_strip names strips for it): output rows and
  * wavefronts per workgroup, as lbm_describe reports them, after lbm_init's
  * timing when tile_rows = -1 (lbm_init then runs the lattice from its
  * initial state for a few launches of each candidate, alternating f_a and f_b
@@ -314,7 +324,8 @@ int lbm_eos_set_knots(lbm_eos* e, double rho_max, double p_max, double rho_min, 
  * grouped launches over every lattice at once or by one persistent launch in
  * which one workgroup owns one lattice and loops over the steps (see
  * lbm_step_batched and lbm_set_batch_mode for which runs when).  Either is
- * captured in HIP graphs and replayed.  Population buffers
+ * captured in HIP graphs and replayed; batches of short lattices run the strip
+ * kernel instead, launched directly.  Population buffers
  * hold the lattices back to back (lbm_batch_layout gives the sizes); scalar
  * fields are packed in lattice order, lattice b occupying
  * [cell_offsets[b], cell_offsets[b+1]) as [ny_b][nx_b].

@@ -818,6 +818,18 @@ int lbm_describe(const lbm_params* p, int* variant_out, int* band_rows_out, int*
     return LBM_OK;
 }
 
+int lbm_describe_strip(const lbm_params* p, int* threads_out, int* steps_out)
+{
+    if (!p || p->nx < 1 || p->ny < 1) {
+        lbm_set_error("lbm_describe_strip: invalid lattice size");
+        return LBM_EINVAL;
+    }
+    const StripPlan s = lattice_strip_plan(*p);
+    if (threads_out) *threads_out = s.threads;
+    if (steps_out) *steps_out = s.steps;
+    return LBM_OK;
+}
+
 int lbm_tile_shape(const lbm_ctx* c, int* rows_out, int* waves_out)
 {
     if (!c || !c->blk2) {
@@ -931,8 +943,7 @@ int init_ctx(lbm_ctx* c, const lbm_params* p, void* f_a, void* f_b, void* ws, si
     c->red = (double*)(c->ws + kRedOff);
     c->hist_count = 0;
     c->shape = run_shape(*p);
-    // the automatic variant only: an explicit one, or a named tile height, runs what it names
-    c->strip = p->kernel_variant == LBM_VARIANT_AUTO && p->tile_rows == 0 ? strip_plan(1, p) : StripPlan{0, 0};
+    c->strip = lattice_strip_plan(*p);
     fill_args(c);
     hipStream_t s = (hipStream_t)stream;
     const unsigned init_err[2] = {0u, 0xffffffffu};

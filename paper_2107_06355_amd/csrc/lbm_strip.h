@@ -96,6 +96,13 @@ inline StripPlan strip_plan(int B, const lbm_params* p)
     return best;
 }
 
+// The plan of a single lattice (lbm_init): of the automatic variant only, since an explicit one, or a
+// named or timed tile height, runs what it names
+inline StripPlan lattice_strip_plan(const lbm_params& p)
+{
+    return p.kernel_variant == LBM_VARIANT_AUTO && p.tile_rows == 0 ? strip_plan(1, &p) : StripPlan{0, 0};
+}
+
 // Whether a single lattice leaves a launch of `steps` steps to the strip kernel.  One and two steps
 // run on the one- and two-step kernels, whose smaller workgroups take less time for so little work,
 // except on wide lattices of so few rows that tiles of 10 and more are mostly empty and yet more

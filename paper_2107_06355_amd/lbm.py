@@ -85,6 +85,7 @@ def _signatures():
         "lbm_describe": ([C.POINTER(LbmParams), C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)], i),
         "lbm_init": ([C.POINTER(vp), C.POINTER(LbmParams), vp, vp, vp, sz, vp, vp, vp, vp], i),
         "lbm_init_static": ([C.POINTER(vp), C.POINTER(LbmParams), vp, vp, vp, vp, vp, vp], i),
+        "lbm_describe_strip": ([C.POINTER(LbmParams), C.POINTER(C.c_int), C.POINTER(C.c_int)], i),
         "lbm_tile_shape": ([vp, C.POINTER(C.c_int), C.POINTER(C.c_int)], i),
         "lbm_step": ([vp, C.c_int64, vp], i),
         "lbm_status_check": ([vp, vp], i),
@@ -229,6 +230,13 @@ def describe(P: LbmParams) -> tuple[int, int, int]:
     return v.value, b.value, w.value
 
 
+def describe_strip(P: LbmParams) -> tuple[int, int]:
+    """(threads per workgroup, most steps per launch) of the strip kernel that runs P, (0, 0) if none does."""
+    t, n = C.c_int(0), C.c_int(0)
+    _check(load().lbm_describe_strip(C.byref(P), C.byref(t), C.byref(n)), "lbm_describe_strip")
+    return t.value, n.value
+
+
 # ---------------------------------------------------------------------------- lattice
 class Lattice:
     """A lattice whose populations live in two torch byte tensors on a HIP device (one for
@@ -296,7 +304,8 @@ class Lattice:
         _check(load().lbm_status_check(self._h, self._s()), "lbm_status_check")
 
     def tile_shape(self) -> tuple[int, int]:
-        """(output rows, wavefronts per workgroup) of the two-step tile this lattice runs."""
+        """(output rows, wavefronts per workgroup) of the two-step tile this lattice runs (where it runs
+        two steps at a time, if describe_strip names strips for it)."""
         r, w = C.c_int(0), C.c_int(0)
         _check(load().lbm_tile_shape(self._h, C.byref(r), C.byref(w)), "lbm_tile_shape")
         return r.value, w.value
