@@ -514,9 +514,7 @@ size_t ws_layout(int nwork, size_t* off_part, size_t* off_hist)
     o += ((size_t)nwork * 3 * sizeof(double) + 255) & ~(size_t)255;
     o += (size_t)kRedBlocks * 3 * sizeof(double);  // per-block sums of the two-pass reduction
     *off_hist = o;
-    o += (size_t)kHistCap * 4 * sizeof(double);
-    o += 256;
-    return o;
+    return o + (size_t)kHistCap * 4 * sizeof(double);
 }
 
 void fill_args(lbm_ctx* c)
