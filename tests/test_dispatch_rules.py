@@ -105,3 +105,18 @@ def test_timed_tiles_include_the_one_that_runs_untimed(rules, prec):
             picks.add(pick[0])
             assert set(range(7, 11) if prec == 0 else [10] + list(range(14, 19))) <= {r for r, _ in cand}, (nx, ny, got)
     assert picks & ({5, 6} if prec == 0 else {12})  # heights outside the timed range were among them
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_the_batches_tested_against_the_oracle_are_cut(rules, prec):
+    """What tests/test_gpu_batched_paths.py relies on: strips of 8 steps, with a last one of one column,
+    beside resident lattices."""
+    from test_gpu_batched_paths import CUT
+
+    sizes = [v for s in CUT for v in s]
+    assert rules([(prec, 8, len(CUT), *sizes)])[0][1] == 8
+    got = rules([(prec, 8, len(CUT), *sizes)])[0][3:]
+    cols, out = got[0::2], got[1::2]
+    cut = [c < nx for (nx, _), c in zip(CUT, cols)]
+    assert cut == [False, True, True, True, False]
+    assert CUT[1][0] % out[1] == 1
