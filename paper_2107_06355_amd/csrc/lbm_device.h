@@ -1085,7 +1085,7 @@ __device__ __forceinline__ void step2_tile_rows(const StepArgs& A, int strip, in
     // 1. step t: pull, rho, psi.  The EOS record is copied to LDS while the pull is in
     //    flight: psi reads it there in phases 1 and 3, instead of the launch holding it in
     //    scalar registers (which spills them to vector lanes at this occupancy).  Even its
-    //    base and shape: two scalar registers more spilled 4 (8192^2 FP32 567 -> 573 us/step;
+    //    base and shape: two scalar registers more spilled 4 (8192^2 FP32 609 -> 612 us/step;
     //    the one-row kernel has room for them and gains 1.3% at 512^2).
     if (threadIdx.x == 0) S.eos = A.eos;
     // With ALL every row loads, one that is not needed (or is solid) from a row that is there: a
