@@ -65,13 +65,14 @@ __device__ __forceinline__ void fd_flag(const FdArgs& A)
 // on the tile grown by 2 (region R2).  Ghost rows beyond the walls are
 // written into both regions by the wall rules, so every stencil reads LDS
 // with the same offsets.  Traffic per node-step: the state read once (plus
-// the four-node ring, mostly from L2) and written once.
+// the four-node ring, mostly from L2) and written once, and 28 bytes per thread of spilled registers.
 //
-// What bounds it: on large meshes FP64 issue, LDS reads (41 per right-hand side) and traffic
-// take about 60% of the launch each; at 512^2, two workgroups per CU in one round, the phases'
-// latency comes on top.  Measured (MI355X, us/step), with 512 threads and two rounds of predictor
-// nodes, divided differences and integer remainders -> now: 512^2 10.6 -> 9.5, 2048^2 114 -> 99,
-// 700 x 500 with walls and tau(rho) 17.1 -> 15.4, 200^2 7.3 -> 6.0.  Two nodes per thread share 30
+// What bounds it (counters): at 512^2, two workgroups per CU in one round, latency: of 9.6 us, VALU
+// issue takes 3.7 and LDS reads (41 per right-hand side) 3.5, and the waves wait half of their
+// time.  At 4096^2, 445 us, issue takes 53%, LDS 50%, and the traffic, 1.70 GB, runs at 77% of the copy
+// rate; 0.47 GB of it are the spilled registers' writes.  Measured (MI355X, us/step), with 512 threads
+// and two rounds of predictor nodes, divided differences and integer remainders -> now: 512^2 10.6 ->
+// 9.5, 2048^2 114 -> 99, 700 x 500 with walls and tau(rho) 17.1 -> 15.4, 200^2 7.3 -> 6.0.  Two nodes per thread share 30
 // of 82 LDS reads but take 168 registers (12 instead of 24 waves per CU): 2048^2 140.
 constexpr int kTx = 32, kTy = 16;
 constexpr int kAx = kTx + 8, kAy = kTy + 8;   // R4
@@ -123,8 +124,8 @@ __device__ __forceinline__ void fd_rhs(const FdArgs& A, const double* R, const d
     }
     Sx += k * (Dx + r * Ex) + kB * (Bx + r * Fx);
     Sy += k * (Dy + r * Ey) + kB * (By + r * Fy);
-    // psi's reads stay behind the velocity's arithmetic: with all 41 in flight the kernel spills
-    // at the 80 registers of 24 waves per CU (512^2 9.7 us/step instead of 9.5)
+    // psi's reads stay behind the velocity's arithmetic: with all 41 in flight the kernel spills more
+    // than 8 of the 80 registers of 24 waves per CU (512^2 9.7 us/step instead of 9.5)
     __builtin_amdgcn_sched_barrier(0);
     // Eq. FDforce, central differences of psi (the Laplacian at x+-1, y+-1 reaches two nodes out)
     const double s0 = S[c], sxp = S[c + 1], sxm = S[c - 1], syp = S[c + P], sym = S[c - P];
